@@ -35,6 +35,20 @@ template <typename T>
 __device__ __forceinline__ cplx<T> c_mulc(cplx<T> a, cplx<T> b) {
   return {a.x * b.x + a.y * b.y, a.y * b.x - a.x * b.y};
 }
+// The same with the contraction written out, as the compiler chooses it in
+// fft_stage: which of the two products it rounds depends on the code around.
+__device__ __forceinline__ float mad(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double mad(double a, double b, double c) {
+  return __builtin_fma(a, b, c);
+}
+template <typename T>
+__device__ __forceinline__ cplx<T> c_mul_fma(cplx<T> a, cplx<T> b) {
+  return {mad(a.x, b.x, -(a.y * b.y)), mad(a.y, b.x, a.x * b.y)};
+}
+template <typename T>
+__device__ __forceinline__ cplx<T> c_mulc_fma(cplx<T> a, cplx<T> b) {
+  return {mad(a.x, b.x, a.y * b.y), mad(a.y, b.x, -(a.x * b.y))};
+}
 template <typename T>
 __device__ __forceinline__ cplx<T> c_conj(cplx<T> a) { return {a.x, -a.y}; }
 template <typename T>
@@ -272,12 +286,134 @@ __device__ __forceinline__ void fft_pencil(cplx<T>* buf, int stride, int lane,
 }
 
 // ---------------------------------------------------------------------------
+// The same stages by a whole workgroup, in two phases with the stages of each
+// in registers: N = N1 N2, N1 the product of the first fft_split(N) radices.
+// Phase one takes the N1 elements m + N2 r of one residue m through its stages
+// (an N1-point Stockham transform whose span starts at 1) and leaves them at
+// m N1 + j; phase two takes the N2 elements m N1 + j of one j through the
+// remaining stages and leaves them at j + N1 t, the places it read.  Every
+// butterfly and twiddle is that of fft_pencil, so the results are the same
+// bits.  fft_pencil gives a pencil fft_lanes(N) lanes (2 for 36 points, 4 for
+// 72) and goes through LDS once per stage; here a 72 x 72 column is 648 and 576
+// tasks, and goes through LDS twice per transform.
+// ---------------------------------------------------------------------------
+__host__ __device__ constexpr int fft_split(int N) {
+  return N == 12 || N == 18 || N == 36 || N == 96 ? 2 : N == 72 ? 3 : 1;
+}
+__host__ __device__ constexpr int fft_n1(int N) { return fft_span(N, fft_split(N)); }
+__host__ __device__ constexpr int fft_n2(int N) { return N / fft_n1(N); }
+
+// Stages STAGE .. END-1 of the N-point transform on the NLOC register values
+// of one task; Q is the product of the task's radices so far.  j: the task's
+// offset in phase two (0 in phase one, where twiddles of offset 0 are 1).
+template <typename T, int N, int S, int STAGE, int END, int NLOC, int Q = 1>
+__device__ __forceinline__ void fft_reg_stages(cplx<T>* v, int j, const cplx<T>* tw, int twstep) {
+  if constexpr (STAGE < END) {
+    constexpr int R = fft_radix(N, STAGE), LS = fft_span(N, STAGE), NB = NLOC / R, BASE = LS / Q;
+    cplx<T> o[NLOC];
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+      const int k = b / Q, t = b % Q;
+      cplx<T> x[R];
+#pragma unroll
+      for (int r = 0; r < R; ++r) x[r] = v[b + r * NB];
+      if (LS > 1 && !(BASE == 1 && t == 0)) {
+#pragma unroll
+        for (int r = 1; r < R; ++r) {
+          const cplx<T> w = tw[(j + BASE * t) * r * (N / (LS * R)) * twstep];
+          x[r] = S < 0 ? c_mul_fma(x[r], w) : c_mulc_fma(x[r], w);
+        }
+      }
+      Dft<R, S, T>::run(x);
+#pragma unroll
+      for (int u = 0; u < R; ++u) o[k * Q * R + t + u * Q] = x[u];
+    }
+#pragma unroll
+    for (int i = 0; i < NLOC; ++i) v[i] = o[i];
+    fft_reg_stages<T, N, S, STAGE + 1, END, NLOC, Q * R>(v, j, tw, twstep);
+  }
+}
+
+// In-place N-point transforms of NPEN pencils (element k of pencil p at
+// buf[p * pstride + k * estride]) by a workgroup of NT threads.  read(p, k)
+// gives the elements phase one starts from (the buffer's own, or what a caller
+// forms from them).  Neighbouring lanes take neighbouring pencils: without
+// bank conflicts for pstride 1 or odd.  All threads call it; it synchronises
+// before its first write and at its end, not before its first read.
+template <typename T, int N, int S, int NPEN, int NT, class Read>
+__device__ __forceinline__ void block_fft(cplx<T>* buf, int pstride, int estride, const cplx<T>* tw,
+                                          int twstep, Read&& read) {
+  constexpr int N1 = fft_n1(N), N2 = fft_n2(N), SPLIT = fft_split(N), NS = fft_nstages(N);
+  constexpr int T1 = NPEN * N2, TPT = (T1 + NT - 1) / NT, T2 = NPEN * N1;
+  const int tid = threadIdx.x;
+  cplx<T> v[TPT][N1];
+#pragma unroll
+  for (int i = 0; i < TPT; ++i) {
+    const int task = tid + i * NT;
+    if (T1 % NT == 0 || task < T1) {
+      const int p = task % NPEN, m = task / NPEN;
+#pragma unroll
+      for (int r = 0; r < N1; ++r) v[i][r] = read(p, m + N2 * r);
+      fft_reg_stages<T, N, S, 0, SPLIT, N1>(v[i], 0, tw, twstep);
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < TPT; ++i) {
+    const int task = tid + i * NT;
+    if (T1 % NT == 0 || task < T1) {
+      const int p = task % NPEN, m = task / NPEN;
+#pragma unroll
+      for (int j = 0; j < N1; ++j) buf[p * pstride + (m * N1 + j) * estride] = v[i][j];
+    }
+  }
+  __syncthreads();
+  for (int task = tid; task < T2; task += NT) {
+    const int p = task % NPEN, j = task / NPEN;
+    cplx<T> w[N2];
+#pragma unroll
+    for (int m = 0; m < N2; ++m) w[m] = buf[p * pstride + (m * N1 + j) * estride];
+    fft_reg_stages<T, N, S, SPLIT, NS, N2>(w, j, tw, twstep);
+#pragma unroll
+    for (int t = 0; t < N2; ++t) buf[p * pstride + (j + N1 * t) * estride] = w[t];
+  }
+  __syncthreads();
+}
+template <typename T, int N, int S, int NPEN, int NT>
+__device__ __forceinline__ void block_fft(cplx<T>* buf, int pstride, int estride, const cplx<T>* tw,
+                                          int twstep) {
+  block_fft<T, N, S, NPEN, NT>(buf, pstride, estride, tw, twstep,
+                               [&](int p, int k) { return buf[p * pstride + k * estride]; });
+}
+
+// ---------------------------------------------------------------------------
 // Real-to-complex along a row of N = 2M reals stored as M packed complex
 // values z_n = x_{2n} + i x_{2n+1}: after the M-point forward FFT Z, the half
 // spectrum is X_k = E_k + W_N^k O_k with E_k = (Z_k + conj Z_{M-k})/2 and
 // O_k = (Z_k - conj Z_{M-k})/(2i), k = 0..M (W_N^M = -1).  Each lane handles
 // the pairs (k, M-k) for k = lane, lane + NT, ... <= M/2.
 // ---------------------------------------------------------------------------
+// Modes k and M - k of the row from Z_k and Z_{M-k} (k = 0: modes 0 and M).
+template <typename T, int N, class Sink>
+__device__ __forceinline__ void r2c_pair(int k, const cplx<T>& zk, const cplx<T>& zm,
+                                         const cplx<T>* twN, Sink&& sink) {
+  constexpr int M = N / 2;
+  cplx<T> e = c_scale(c_add(zk, c_conj(zm)), T(0.5));
+  cplx<T> d = c_sub(zk, c_conj(zm));
+  cplx<T> o = {T(0.5) * d.y, T(-0.5) * d.x};  // d / (2i)
+  if (k == 0) {
+    sink(0, c_add(e, o));
+    sink(M, c_sub(e, o));
+  } else {
+    sink(k, c_add(e, c_mul(twN[k], o)));
+    if (k != M - k) {
+      cplx<T> e2 = c_scale(c_add(zm, c_conj(zk)), T(0.5));
+      cplx<T> d2 = c_sub(zm, c_conj(zk));
+      cplx<T> o2 = {T(0.5) * d2.y, T(-0.5) * d2.x};
+      sink(M - k, c_add(e2, c_mul(twN[M - k], o2)));
+    }
+  }
+}
 template <typename T, int N, class Sink>
 __device__ __forceinline__ void r2c_post(const cplx<T>* row, int lane, const cplx<T>* twN,
                                          Sink&& sink) {
@@ -298,32 +434,8 @@ __device__ __forceinline__ void r2c_post(const cplx<T>* row, int lane, const cpl
 #pragma unroll
   for (int i = 0; i < PPL; ++i) {
     const int k = lane + i * NT;
-    if (k < NP) {
-      // X_k from (Z_k, Z_{M-k}); X_{M-k} from (Z_{M-k}, Z_k)
-      const cplx<T> zk = za[i], zm = zb[i];
-      cplx<T> e = c_scale(c_add(zk, c_conj(zm)), T(0.5));
-      cplx<T> d = c_sub(zk, c_conj(zm));
-      cplx<T> o = {T(0.5) * d.y, T(-0.5) * d.x};  // d / (2i)
-      if (k == 0) {
-        sink(0, c_add(e, o));
-        sink(M, c_sub(e, o));
-      } else {
-        sink(k, c_add(e, c_mul(twN[k], o)));
-        if (k != M - k) {
-          cplx<T> e2 = c_scale(c_add(zm, c_conj(zk)), T(0.5));
-          cplx<T> d2 = c_sub(zm, c_conj(zk));
-          cplx<T> o2 = {T(0.5) * d2.y, T(-0.5) * d2.x};
-          sink(M - k, c_add(e2, c_mul(twN[M - k], o2)));
-        }
-      }
-    }
+    if (k < NP) r2c_pair<T, N>(k, za[i], zb[i], twN, sink);
   }
-}
-// ... in place: X_0 .. X_M into the row.
-template <typename T, int N>
-__device__ __forceinline__ void r2c_post(cplx<T>* row, int lane, const cplx<T>* twN) {
-  r2c_post<T, N>(row, lane, twN, [&](int k, const cplx<T>& x) { row[k] = x; });
-  lds_order();
 }
 
 // Complex-to-real preparation: from the half spectrum X_0..X_M of a real
@@ -331,42 +443,16 @@ __device__ __forceinline__ void r2c_post(cplx<T>* row, int lane, const cplx<T>* 
 // and B_k = (X_k - conj X_{M-k}) exp(+2 pi i k/N); the M-point inverse FFT of
 // Y then holds x_{2n} + i x_{2n+1} (unnormalised).  Im X_0 and Im X_M are
 // exactly zero for a real row and are dropped.
-template <typename T, int N>
-__device__ __forceinline__ void c2r_pre(cplx<T>* row, int lane, const cplx<T>* twN) {
-  constexpr int M = N / 2;
-  constexpr int NT = fft_lanes(M);
-  constexpr int NP = M / 2 + 1;
-  constexpr int PPL = (NP + NT - 1) / NT;
-  cplx<T> xa[PPL], xb[PPL];
-#pragma unroll
-  for (int i = 0; i < PPL; ++i) {
-    const int k = lane + i * NT;
-    if (k < NP) {
-      xa[i] = row[k];
-      xb[i] = row[M - k];
-    }
+// Y_k from X_k and X_{M-k}.
+template <typename T>
+__device__ __forceinline__ cplx<T> c2r_mode(int k, cplx<T> xk, cplx<T> xm, const cplx<T>* twN) {
+  if (k == 0) {
+    xk.y = T(0);
+    xm.y = T(0);
   }
-  lds_order();
-#pragma unroll
-  for (int i = 0; i < PPL; ++i) {
-    const int k = lane + i * NT;
-    if (k < NP) {
-      cplx<T> xk = xa[i], xm = xb[i];
-      if (k == 0) {
-        xk.y = T(0);
-        xm.y = T(0);
-      }
-      cplx<T> a = c_add(xk, c_conj(xm));
-      cplx<T> b = c_mulc(c_sub(xk, c_conj(xm)), twN[k]);
-      row[k] = {a.x - b.y, a.y + b.x};  // A + i B
-      if (k != 0 && k != M - k) {
-        cplx<T> a2 = c_add(xm, c_conj(xk));
-        cplx<T> b2 = c_mulc(c_sub(xm, c_conj(xk)), twN[M - k]);
-        row[M - k] = {a2.x - b2.y, a2.y + b2.x};
-      }
-    }
-  }
-  lds_order();
+  const cplx<T> am = c_add(xk, c_conj(xm));
+  const cplx<T> bm = c_mulc(c_sub(xk, c_conj(xm)), twN[k]);
+  return {am.x - bm.y, am.y + bm.x};  // A + i B
 }
 
 // ---------------------------------------------------------------------------

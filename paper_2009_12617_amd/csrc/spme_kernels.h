@@ -144,10 +144,10 @@ struct Grid {
 // FP64: room for K/2+1 double2.  The padding skews rows across LDS banks.
 template <class P>
 __host__ __device__ constexpr int tile_pitch(int K) {
-  // chosen with a bank model of the x transform's Stockham stages over rows
-  // of this pitch (64-lane wavefront, 4-byte banks)
-  return P::fixed ? (K == 32 ? 34 : K == 64 ? 66 : K == 96 ? 98 : K == 128 ? 135 : K + 1)
-                  : 2 * (K == 128 ? 71 : K / 2 + 1);
+  // an odd number of 8-byte (FP64: 16-byte) units where the x transform takes
+  // one row per lane; at 64 and 128 points chosen with a bank model of the
+  // register transforms' transposes (64-lane wavefront, 4-byte banks)
+  return P::fixed ? (K == 64 ? 66 : K == 128 ? 135 : K + 1) : 2 * (K == 128 ? 71 : K / 2 + 1);
 }
 
 // Workgroups are dispatched round-robin over the 8 XCDs (each with its own
@@ -387,14 +387,7 @@ __device__ __forceinline__ void c2r_row_reg(cplx<T>* row, int j, cplx<T>* scr, c
 #pragma unroll
     for (int t = 0; t < RX; ++t) {
       const int k = j * EX + e + 8 * t;
-      cplx<T> xk = row[k], xm = row[M - k];
-      if (k == 0) {
-        xk.y = T(0);
-        xm.y = T(0);
-      }
-      const cplx<T> am = c_add(xk, c_conj(xm));
-      const cplx<T> bm = c_mulc(c_sub(xk, c_conj(xm)), tw[k]);
-      v[e * RX + t] = {am.x - bm.y, am.y + bm.x};  // A + i B
+      v[e * RX + t] = c2r_mode(k, row[k], row[M - k], tw);
     }
   RegTw<T, M> w;
   w.template load<2>(j, tw);
@@ -481,7 +474,7 @@ __global__ __launch_bounds__(spread_threads<BATCH>()) void k_spread_x(Args a_in,
   using Acc = typename P::acc;
   using Rec = typename P::rec;
   constexpr int K1 = G::K1, K2 = G::K2, K3 = G::K3;
-  constexpr int M = K1 / 2, KH = K1 / 2 + 1;
+  constexpr int M = K1 / 2;
   constexpr int NQ = nq_of(K2, P::fixed), R = K2 / NQ;
   constexpr int PITCH = tile_pitch<P>(K1);
   constexpr int NBK = 3 * ORDER;  // buckets read per tile
@@ -590,9 +583,9 @@ __global__ __launch_bounds__(spread_threads<BATCH>()) void k_spread_x(Args a_in,
     __syncthreads();  // the x transform below overwrites the tile in place
   }
 
-  // --- x: real-to-complex, one row per group of fft_lanes(M) lanes.
-  constexpr int TM = fft_lanes(M);
+  // --- x: real-to-complex
   if constexpr (reg_x_ok<K1>()) {
+    constexpr int TM = fft_lanes(M);  // lanes per row
     static_assert(TM == M / 8 && R * TM <= NTS, "register x rows");
     if (tid < R * TM) {
       const int y = tid / TM, j = tid - y * TM;
@@ -621,42 +614,32 @@ __global__ __launch_bounds__(spread_threads<BATCH>()) void k_spread_x(Args a_in,
     }
     TRACE(1, 15);
     return;
-  } else
-  for (int task = tid; task < R * TM; task += NTS) {
-    const int y = task / TM, l = task - y * TM;
-    cplx<T>* row = reinterpret_cast<cplx<T>*>(tile + y * PITCH);
+  } else {
+    constexpr int PC = P::fixed ? PITCH : PITCH / 2;
+    cplx<T>* rows = reinterpret_cast<cplx<T>*>(tile);
     if constexpr (P::fixed) {
-      // int64 -> float in place: x_j at float slot j, so the row reads as the
-      // packed complex sequence z_n = x_{2n} + i x_{2n+1}
+      // int64 -> FP64 -> FP32: x_{2n} and x_{2n+1} of the packed sequence
       const double inv_scale = ldexp(1.0, -a.frac_bits);
-      constexpr int PER = K1 / TM;
-      float v[PER];
-#pragma unroll
-      for (int i = 0; i < PER; ++i) {
-        const long long iv = (long long)tile[y * PITCH + l + i * TM];
-        v[i] = (float)((double)iv * inv_scale);
-      }
-      lds_order();
-#pragma unroll
-      for (int i = 0; i < PER; ++i) reinterpret_cast<float*>(row)[l + i * TM] = v[i];
-      lds_order();
+      block_fft<T, M, -1, R, NTS>(rows, PC, 1, tw, 2, [&](int y, int n) -> cplx<T> {
+        const Acc* ri = tile + y * PITCH;
+        return {(float)((double)(long long)ri[2 * n] * inv_scale),
+                (float)((double)(long long)ri[2 * n + 1] * inv_scale)};
+      });
+    } else {
+      block_fft<T, M, -1, R, NTS>(rows, PC, 1, tw, 2);
     }
-    fft_pencil<T, M, -1>(row, 1, l, tw, 2);
-    r2c_post<T, K1>(row, l, tw);
+    TRACE(1, 3);
+    // half spectrum columns [x'][z][y]: runs of R rows per x'
+    using S = typename P::spec;
+    S* spec = reinterpret_cast<S*>(a.ws + a.lay.spec) + (size_t)z * K2 + y0;
+    for (int i = tid; i < R * (M / 2 + 1); i += NTS) {
+      const int k = i / R, y = i - k * R;
+      r2c_pair<T, K1>(k, rows[y * PC + k], rows[y * PC + (M - k) % M], tw, [&](int x, const cplx<T>& v) {
+        spec_st(&spec[(size_t)x * K3 * K2 + y], v);
+      });
+    }
+    TRACE(1, 15);
   }
-  __syncthreads();
-  TRACE(1, 3);
-
-  // half spectrum columns [x'][z][y]: runs of R rows per x'
-  using S = typename P::spec;
-  S* spec = reinterpret_cast<S*>(a.ws + a.lay.spec) + (size_t)z * K2 + y0;
-  constexpr int PC = P::fixed ? PITCH : PITCH / 2;
-  const cplx<T>* tc = reinterpret_cast<const cplx<T>*>(tile);
-  for (int i = tid; i < R * KH; i += NTS) {
-    const int x = i / R, y = i - x * R;
-    spec_st(&spec[(size_t)x * K3 * K2 + y], tc[y * PC + x]);
-  }
-  TRACE(1, 15);
 }
 
 // ---------------------------------------------------------------------------
@@ -691,9 +674,8 @@ __host__ __device__ constexpr size_t conv_tables_bytes() {
   return (size_t)(G::K2 + G::K3) * sizeof(cplx<typename P::real>) +
          (size_t)(G::K1 + G::K2 + G::K3) * sizeof(double) + 16 * 8 * sizeof(double);
 }
-// Row pitch (complex elements) of the column in LDS: rows are y pencils of
-// K points, columns z pencils; chosen with a bank model of the Stockham
-// stages over both (64-lane wavefront, 4-byte banks).
+// Row pitch (complex elements) of k_conv_y's rows of K points; chosen with a
+// bank model of the Stockham stages (64-lane wavefront, 4-byte banks).
 template <class P>
 __host__ __device__ constexpr int conv_pitch(int K) {
   return sizeof(typename P::real) == 4
@@ -710,15 +692,17 @@ __host__ __device__ constexpr int conv_nchunks() {
              ? 1
              : 2;
 }
-// z pass row pitch when the column is staged in chunks
+// Row pitch of k_conv (odd: its passes take one pencil per lane), and of its
+// z pass when the column is staged in chunks
+__host__ __device__ constexpr int conv_row(int K) { return K + 1; }
 template <class P, class G>
 __host__ __device__ constexpr int conv_zpitch() {
-  return conv_nchunks<P, G>() == 1 ? conv_pitch<P>(G::K2) : G::K2 / 2 + 3;
+  return conv_nchunks<P, G>() == 1 ? conv_row(G::K2) : G::K2 / 2 + 3;
 }
 template <class P, class G>
 __host__ __device__ constexpr size_t conv_buf_bytes() {
   constexpr size_t NC = conv_nchunks<P, G>();
-  constexpr size_t ny = (G::K3 / NC) * conv_pitch<P>(G::K2), nz = (size_t)G::K3 * conv_zpitch<P, G>();
+  constexpr size_t ny = (G::K3 / NC) * conv_row(G::K2), nz = (size_t)G::K3 * conv_zpitch<P, G>();
   return (ny > nz ? ny : nz) * sizeof(cplx<typename P::real>);
 }
 template <class P, class G>
@@ -934,8 +918,8 @@ __device__ __forceinline__ void ev_row(const Args& a, double* acc, int r) {
 
 template <class P, class G, bool BATCH>
 __global__ __launch_bounds__((conv_block<P, G, BATCH>()),
-                             (conv_block<P, G, BATCH>() == 512 ? 4 : 1)) void k_conv(Args a_in,
-                                                                                      BatchArgs bt) {
+                             (conv_block<P, G, BATCH>() == 512 ? (P::fixed ? 4 : 2) : 1)) void
+k_conv(Args a_in, BatchArgs bt) {
   const Args a = BATCH ? *bt.sys[blockIdx.y] : a_in;
   using T = typename P::real;
   constexpr int K1 = G::K1, K2 = G::K2, K3 = G::K3;
@@ -943,9 +927,8 @@ __global__ __launch_bounds__((conv_block<P, G, BATCH>()),
   constexpr int NC = conv_nchunks<P, G>();
   constexpr int CZ = K3 / NC;                  // z-planes per chunk (y passes)
   constexpr int CY = K2 / NC;                  // y rows per chunk (z pass)
-  constexpr int PY = conv_pitch<P>(K2);        // y pass: one row of pitch PY per z
+  constexpr int PY = conv_row(K2);             // y pass: one row of pitch PY per z
   constexpr int PZ = conv_zpitch<P, G>();      // z pass: one row of pitch PZ per z
-  constexpr int TY = fft_lanes(K2), TZ = fft_lanes(K3);
   constexpr int NT = conv_block<P, G, BATCH>();
   // the modes are dealt to VT virtual threads, NV per thread, as a VT-thread
   // launch deals them, so that batched and single steps add alike
@@ -1000,11 +983,7 @@ __global__ __launch_bounds__((conv_block<P, G, BATCH>()),
       }
     }
     __syncthreads();
-    for (int task = tid; task < CZ * TY; task += NT) {
-      const int zz = task / TY, l = task - zz * TY;
-      fft_pencil<T, K2, -1>(buf + zz * PY, 1, l, twy, 1);
-    }
-    __syncthreads();
+    block_fft<T, K2, -1, CZ, NT>(buf, PY, 1, twy, 1);
     if constexpr (NC > 1) {
       for (int i = tid; i < CZ * K2; i += NT) {
         const int zz = i / K2, y = i - zz * K2;
@@ -1030,11 +1009,7 @@ __global__ __launch_bounds__((conv_block<P, G, BATCH>()),
       }
       __syncthreads();
     }
-    for (int task = tid; task < CY * TZ; task += NT) {
-      const int yy = task / TZ, l = task - yy * TZ;
-      fft_pencil<T, K3, -1>(buf + yy, PZ, l, twz, 1);
-    }
-    __syncthreads();
+    block_fft<T, K3, -1, CY, NT>(buf, 1, PZ, twz, 1);
     TRACE(2, 2);
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
@@ -1044,11 +1019,7 @@ __global__ __launch_bounds__((conv_block<P, G, BATCH>()),
     }
     __syncthreads();
     TRACE(2, 3);
-    for (int task = tid; task < CY * TZ; task += NT) {
-      const int yy = task / TZ, l = task - yy * TZ;
-      fft_pencil<T, K3, 1>(buf + yy, PZ, l, twz, 1);
-    }
-    __syncthreads();
+    block_fft<T, K3, 1, CY, NT>(buf, 1, PZ, twz, 1);
     if constexpr (NC > 1) {
       for (int i = tid; i < K3 * CY; i += NT) {
         const int z = i / CY, yy = i - z * CY;
@@ -1069,11 +1040,7 @@ __global__ __launch_bounds__((conv_block<P, G, BATCH>()),
       }
       __syncthreads();
     }
-    for (int task = tid; task < CZ * TY; task += NT) {
-      const int zz = task / TY, l = task - zz * TY;
-      fft_pencil<T, K2, 1>(buf + zz * PY, 1, l, twy, 1);
-    }
-    __syncthreads();
+    block_fft<T, K2, 1, CZ, NT>(buf, PY, 1, twy, 1);
     for (int i = tid; i < CZ * K2; i += NT) {
       const int zz = i / K2, y = i - zz * K2;
       spec_st(&col[(size_t)(z0 + zz) * K2 + y], buf[zz * PY + y]);
@@ -1403,12 +1370,12 @@ static __device__ void reduce_ev(const Args& a) {
 // large grids before k_interp_phi, and for the debug copy of the potential.
 // ---------------------------------------------------------------------------
 // Row pitch (complex) of the potential rows of k_inv_x and k_interp: the
-// half spectrum X_0 .. X_{K1/2} plus one, widened where the register
-// inverse x transform uses the row itself as its transpose scratch (RX
-// lanes of 9 complex each).
+// half spectrum X_0 .. X_{K1/2} (odd: the transform takes one row per lane),
+// plus one and widened where the register inverse x transform uses the row
+// itself as its transpose scratch (RX lanes of 9 complex each).
 template <int K1>
 __host__ __device__ constexpr int x_row_pitch() {
-  return reg_x_ok<K1>() && (K1 / 16) * 9 > K1 / 2 + 2 ? (K1 / 16) * 9 : K1 / 2 + 2;
+  return !reg_x_ok<K1>() ? K1 / 2 + 1 : (K1 / 16) * 9 > K1 / 2 + 2 ? (K1 / 16) * 9 : K1 / 2 + 2;
 }
 template <class P, class G, int ORDER>
 __host__ __device__ constexpr size_t inv_x_lds_bytes() {
@@ -1445,15 +1412,12 @@ __global__ __launch_bounds__(kPlaneThreads) void k_inv_x(Args a_in, BatchArgs bt
       const int y = task / TM, l = task - y * TM;
       c2r_row_reg<T, K1>(pl + y * PC, l, pl + y * PC, tw);  // the row is its scratch
     }
+    __syncthreads();
   } else {
-    for (int task = tid; task < K2 * TM; task += kPlaneThreads) {
-      const int y = task / TM, l = task - y * TM;
-      cplx<T>* row = pl + y * PC;
-      c2r_pre<T, K1>(row, l, tw);
-      fft_pencil<T, M, 1>(row, 1, l, tw, 2);
-    }
+    block_fft<T, M, 1, K2, kPlaneThreads>(pl, PC, 1, tw, 2, [&](int y, int k) {
+      return c2r_mode(k, pl[y * PC + k], pl[y * PC + M - k], tw);
+    });
   }
-  __syncthreads();
   T* phi = reinterpret_cast<T*>(a.ws + a.lay.phi) + (size_t)z * K2 * PP;
   for (int i = tid; i < K2 * PP; i += kPlaneThreads) {
     const int y = i / PP, xh = i - y * PP;
@@ -1603,14 +1567,12 @@ __global__ __launch_bounds__(kInterpThreads) void k_interp(Args a_in, BatchArgs 
       const int row = task / TM, l = task - row * TM;
       c2r_row_reg<T, K1>(buf + row * PC, l, buf + row * PC, tw);  // the row is its scratch
     }
+    __syncthreads();
   } else {
-    for (int task = tid; task < NROW * TM; task += NT) {
-      const int row = task / TM, l = task - row * TM;
-      c2r_pre<T, K1>(buf + row * PC, l, tw);
-      fft_pencil<T, M, 1>(buf + row * PC, 1, l, tw, 2);
-    }
+    block_fft<T, M, 1, NROW, NT>(buf, PC, 1, tw, 2, [&](int row, int k) {
+      return c2r_mode(k, buf[row * PC + k], buf[row * PC + M - k], tw);
+    });
   }
-  __syncthreads();
   TRACE(3, 2);
   auto gather = [&](const Rec& rr) {
     const int gx = rr.g & 1023, gy = (rr.g >> 10) & 1023;

@@ -1,0 +1,62 @@
+"""Transforms taken by a whole workgroup (two register phases of each row or
+pencil): the x rows against numpy's FFT of the same charge grid, and the fused
+y/z column against the split passes, which transform one pencil per few lanes
+with the same butterflies and therefore give the same bits.
+
+The x bound: each of the at most 5 stages of a 48-point row, and the
+real-to-complex step behind them, rounds a value by a few units u of the last
+place, so ||err|| / ||spectrum|| <= 6 stages x 8 u = 48 u (2.9e-6 in FP32,
+5.4e-15 in FP64; the rounding of the fixed-point grid to FP32 is one more u).
+"""
+import numpy as np
+import pytest
+import torch
+
+from paper_2009_12617_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def P():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU visible")
+    import paper_2009_12617_amd as pkg
+    return pkg
+
+
+def plan_and_inputs(P, shape, precision, p=4):
+    pos, q, _ = I.water_box(200, 0.8 * shape[0], 40 + sum(shape))
+    edges = 0.8 * np.asarray(shape, dtype=np.float64)
+    pos = pos * (edges / edges[0])
+    plan = P.Plan(shape, p, 0.34, max_atoms=len(q), precision=precision)
+    d = [torch.from_numpy(np.ascontiguousarray(a, dtype=np.float64)).to("cuda") for a in (pos, q)]
+    return plan, d[0], d[1], np.diag(edges)
+
+
+@pytest.mark.parametrize("precision,bound", [("fp32_fixed", 49 * 2.0 ** -24), ("fp64", 48 * 2.0 ** -53)])
+@pytest.mark.parametrize("shape", [(16,) * 3, (24,) * 3, (32,) * 3, (36,) * 3, (48,) * 3, (72,) * 3,
+                                   (96,) * 3, (48, 32, 64)], ids=str)
+def test_x_rows(P, shape, precision, bound):
+    plan, pos, q, box = plan_and_inputs(P, shape, precision)
+    plan.set_debug(True)
+    plan.spread(pos, q, box)
+    grid = plan.debug_grid(0).cpu().numpy().astype(np.float64)
+    if precision != "fp64":
+        grid /= 2.0 ** plan.frac_bits
+    want = np.fft.rfft(grid, axis=2).transpose(2, 0, 1)
+    got = plan.debug_grid(1).cpu().numpy()
+    assert np.linalg.norm(got - want) <= bound * np.linalg.norm(want)
+
+
+@pytest.mark.parametrize("shape", [(64,) * 3, (96,) * 3, (128,) * 3, (32, 32, 64), (64, 64, 128),
+                                   (48, 32, 64)], ids=str)
+def test_fused_column_has_the_bits_of_the_split_passes(P, shape):
+    plan, pos, q, box = plan_and_inputs(P, shape, "fp32_fixed")
+    out = []
+    for conv in (0, 1):
+        plan.set_tuning(conv=conv, interp=1)
+        forces, ev = plan.step(pos, q, box)
+        out.append((forces.cpu().numpy(), ev.cpu().numpy()))
+    assert np.array_equal(out[0][0], out[1][0])
+    assert np.allclose(out[0][1], out[1][1], rtol=1e-12, atol=1e-13 * abs(out[0][1][0]))
