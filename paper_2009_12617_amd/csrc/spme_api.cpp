@@ -352,8 +352,8 @@ int pme_spread(pme_plan* p, const double* pos, const double* q, int N, const dou
 
 namespace {
 
-// The convolution writes one energy/virial row per column; the rows are
-// summed either by the next launch of the step (fused = true) or by a
+// The convolution writes energy/virial rows; the split convolution's last
+// launch sums them, otherwise the next launch of the step (fused = true) or a
 // one-workgroup kernel right away.
 int solve_impl(pme_plan* p, double* ev, bool fused) {
   // exactly once per spread: the convolution transforms the spectrum in
@@ -361,15 +361,14 @@ int solve_impl(pme_plan* p, double* ev, bool fused) {
   if (p->state != kSpread) return PME_ESTATE;
   Args& a = p->cur;
   a.ev = ev;
-  a.reduce_ev = 0;
+  a.reduce_ev = ev != nullptr ? 1 : 0;
   int rc = timed(p, 2, [&](const spme::Timing& t) { return spme::launch_conv(a, p->stream, t); });
   if (rc != PME_OK) p->state = kDirty;
   if (rc != PME_OK) return rc;
-  if (ev != nullptr) {
-    if (fused)
-      a.reduce_ev = 1;
-    else
+  if (!fused) {
+    if (a.reduce_ev && a.conv_mode != spme::kConvSplit)
       rc = device_error(spme::launch_reduce_ev(a, p->stream));
+    a.reduce_ev = 0;
   }
   if (rc != PME_OK) return rc;
   p->state = kSolved;

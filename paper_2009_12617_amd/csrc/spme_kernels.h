@@ -481,10 +481,9 @@ __global__ __launch_bounds__(spread_threads<BATCH>()) void k_spread_x(Args a_in,
   extern __shared__ __align__(16) unsigned char smem[];
   Acc* tile = reinterpret_cast<Acc*>(smem);
   cplx<T>* tw = reinterpret_cast<cplx<T>*>(smem + (size_t)R * PITCH * 8);
-  int* bk_pre = reinterpret_cast<int*>(tw + K1);  // [NBK + 1] item offsets
-  int* bk_base = bk_pre + 24;                     // [NBK] first record
-  int* bk_n = bk_base + 20;                       // [NBK] counts, then the overflow count
-  cplx<T>* xscr = reinterpret_cast<cplx<T>*>(bk_pre + 64);  // register x transforms
+  int* bk_off = reinterpret_cast<int*>(tw + K1);  // [NBK] first record, less the items before
+  int* bk_end = bk_off + 20;  // [NBK] items up to each bucket's end, then the overflow count
+  cplx<T>* xscr = reinterpret_cast<cplx<T>*>(bk_off + 64);  // register x transforms
 
   TRACE(1, 0);
   static_assert((K3 * NQ) % kXcds == 0, "spreading tiles do not split over the XCDs");
@@ -501,42 +500,47 @@ __global__ __launch_bounds__(spread_threads<BATCH>()) void k_spread_x(Args a_in,
   // head (first p-1 rows) of the next slice: an atom touches rows
   // g_y-p+1 .. g_y.  Bucket k = 3j + d: d = 0 own head, 1 own body, 2 next
   // slice's head.
-  if (tid < NBK) {
-    const int j = tid / 3, d = tid - 3 * j;
-    int bz = z + j;
-    if (bz >= K3) bz -= K3;
-    int by = qs + (d == 2 ? 1 : 0);
-    if (by >= NQ) by -= NQ;
-    const int b = (bz * NQ + by) * 2 + (d == 1 ? 1 : 0);
-    bk_n[tid] = min((int)bcnt[b], cap);
-    bk_base[tid] = b * cap;
-  } else if (tid == NBK) {
-    bk_n[NBK] = (int)min(reinterpret_cast<const unsigned*>(a.ws + a.lay.ovf)[0],
-                         (unsigned)a.lay.orec_max);
+  if (tid < 64) {
+    int b = 0, n = 0;
+    if (tid < NBK) {
+      const int j = tid / 3, d = tid - 3 * j;
+      int bz = z + j;
+      if (bz >= K3) bz -= K3;
+      int by = qs + (d == 2 ? 1 : 0);
+      if (by >= NQ) by -= NQ;
+      b = (bz * NQ + by) * 2 + (d == 1 ? 1 : 0);
+      n = min((int)bcnt[b], cap);
+    } else if (tid == NBK) {
+      bk_end[NBK] = (int)min(reinterpret_cast<const unsigned*>(a.ws + a.lay.ovf)[0],
+                             (unsigned)a.lay.orec_max);
+    }
+    int end = n;  // the items of the buckets one after another
+#pragma unroll
+    for (int d = 1; d < NBK; d *= 2) {
+      const int below = __shfl_up(end, d);
+      end += tid >= d ? below : 0;
+    }
+    if (tid < NBK) {
+      bk_end[tid] = end;
+      bk_off[tid] = b * cap - (end - n);
+    }
   }
   const cplx<T>* twg = reinterpret_cast<const cplx<T>*>(a.ws + a.lay.tw);
   for (int i = tid; i < K1; i += NTS) tw[i] = twg[i];
   for (int i = tid; i < R * PITCH; i += NTS) tile[i] = Acc(0);
   const double scale = ldexp(1.0, a.frac_bits);
   __syncthreads();
-  if (tid == 0) {
-    int run = 0;
-    for (int k = 0; k < NBK; ++k) {
-      bk_pre[k] = run;
-      run += bk_n[k];
-    }
-    bk_pre[NBK] = run;
-  }
-  __syncthreads();
   TRACE(1, 1);
 
   // items: the records of the buckets one after another; kItems per thread
-  // per pass so that their loads overlap
+  // per pass so that their loads overlap.  (The bucket ends in scalar
+  // registers: at p = 6 the kernel keeps to 64 vector registers, two
+  // workgroups to a CU; 128^3 p = 6 spreading 34.9 -> 30.6 us.)
   constexpr int kItems = 4;
-  const int total = bk_pre[NBK];
-  int pre[NBK + 1];
+  int end[NBK];
 #pragma unroll
-  for (int k = 0; k <= NBK; ++k) pre[k] = bk_pre[k];
+  for (int k = 0; k < NBK; ++k) end[k] = __builtin_amdgcn_readfirstlane(bk_end[k]);
+  const int total = end[NBK - 1];
   for (int it = 0; it < total; it += kItems * NTS) {
     int idx[kItems], jz[kItems];
 #pragma unroll
@@ -544,11 +548,12 @@ __global__ __launch_bounds__(spread_threads<BATCH>()) void k_spread_x(Args a_in,
       const int t = it + u * NTS + tid;
       jz[u] = -1;
       idx[u] = 0;
-      if (t < total) {
+      // (a wavefront without items skips the search)
+      if (__builtin_amdgcn_readfirstlane(t) < total && t < total) {
         int k = 0;
 #pragma unroll
-        for (int kk = 1; kk < NBK; ++kk) k += (t >= pre[kk]) ? 1 : 0;
-        idx[u] = bk_base[k] + (t - bk_pre[k]);
+        for (int kk = 0; kk < NBK - 1; ++kk) k += (t >= end[kk]) ? 1 : 0;
+        idx[u] = bk_off[k] + t;
         jz[u] = ORDER - 1 - k / 3;
       }
     }
@@ -562,7 +567,7 @@ __global__ __launch_bounds__(spread_threads<BATCH>()) void k_spread_x(Args a_in,
   }
   // atoms of full buckets: the whole overflow list, each atom taken if it
   // belongs to this tile
-  const int novf = bk_n[NBK];
+  const int novf = bk_end[NBK];
   for (int o = tid; o < novf; o += NTS) {
     const Rec r = orec[o];
     const int gy = (r.g >> 10) & 1023, gz = (r.g >> 20) & 1023;
@@ -713,8 +718,8 @@ __host__ __device__ constexpr size_t conv_lds_bytes() {
 // Per-axis factors T_a(m) = |b_a(m)|^2 exp(-pi^2 mt^2 / (beta L_a)^2) of an
 // orthorhombic cell (a general cell keeps the bare moduli: its Gaussian does
 // not factor), x then y then z, into bs[K1 + K2 + K3].
-template <class G, int NT>
-__device__ __forceinline__ void axis_factors(const Args& a, double* bs) {
+template <class G>
+__device__ __forceinline__ void axis_factor(const Args& a, double* bs, int i) {
   constexpr int K1 = G::K1, K2 = G::K2, K3 = G::K3;
   constexpr double PI = 3.14159265358979323846;
   const double* bsg = reinterpret_cast<const double*>(a.ws + a.lay.bsq);
@@ -722,15 +727,17 @@ __device__ __forceinline__ void axis_factors(const Args& a, double* bs) {
   // (values selected, not a.invL[ax]: a dynamic index, or a select of
   // addresses, would move a batched run's Args copy to scratch)
   const double il0 = a.invL[0], il1 = a.invL[1], il2 = a.invL[2];
-  for (int i = threadIdx.x; i < K1 + K2 + K3; i += NT) {
-    const int ax = i < K1 ? 0 : i < K1 + K2 ? 1 : 2;
-    const int Ka = ax == 0 ? K1 : ax == 1 ? K2 : K3;
-    const int m = i - (ax == 0 ? 0 : ax == 1 ? K1 : K1 + K2);
-    const int mt = (2 * m <= Ka) ? m : m - Ka;
-    const double il = ax == 0 ? il0 : ax == 1 ? il1 : il2;
-    const double u = mt * il;
-    bs[i] = a.triclinic ? bsg[i] : bsg[i] * exp(-fac * u * u);
-  }
+  const int ax = i < K1 ? 0 : i < K1 + K2 ? 1 : 2;
+  const int Ka = ax == 0 ? K1 : ax == 1 ? K2 : K3;
+  const int m = i - (ax == 0 ? 0 : ax == 1 ? K1 : K1 + K2);
+  const int mt = (2 * m <= Ka) ? m : m - Ka;
+  const double il = ax == 0 ? il0 : ax == 1 ? il1 : il2;
+  const double u = mt * il;
+  bs[i] = a.triclinic ? bsg[i] : bsg[i] * exp(-fac * u * u);
+}
+template <class G, int NT>
+__device__ __forceinline__ void axis_factors(const Args& a, double* bs) {
+  for (int i = threadIdx.x; i < G::K1 + G::K2 + G::K3; i += NT) axis_factor<G>(a, bs, i);
 }
 
 // The convolution's extra workgroup: keeps the bucket counts of this step
@@ -916,6 +923,37 @@ __device__ __forceinline__ void ev_row(const Args& a, double* acc, int r) {
   }
 }
 
+// Sum of the energy/virial partial rows the step's convolution variant wrote,
+// in a fixed order, by the first kReduceThreads threads of the calling
+// workgroup (whatever its size): thread l adds rows l, l + 256, ..., then a
+// DPP sum over the lanes and the wavefronts' sums in order.  wred: 32 doubles
+// of LDS.  (By one wavefront the 2,080 rows of a split 128^3 column took 13 us.)
+constexpr int kReduceThreads = 256;
+static __device__ void reduce_ev(const Args& a, double* wred) {
+  const int tid = threadIdx.x;
+  const double* partial = reinterpret_cast<const double*>(a.ws + a.lay.partial);
+  double v[7] = {0, 0, 0, 0, 0, 0, 0};
+  if (tid < kReduceThreads) {
+#pragma unroll 4
+    for (int r = tid; r < a.ev_rows; r += kReduceThreads) {
+#pragma unroll
+      for (int c = 0; c < 7; ++c) v[c] += partial[r * 8 + c];
+    }
+    wave_sums<7>(v);
+    if ((tid & 63) == 63) {
+#pragma unroll
+      for (int c = 0; c < 7; ++c) wred[(tid >> 6) * 8 + c] = v[c];
+    }
+  }
+  __syncthreads();
+  if (tid < 7) {
+    double s = 0.0;
+#pragma unroll
+    for (int w = 0; w < kReduceThreads / 64; ++w) s += wred[w * 8 + tid];
+    a.ev[tid] = s;
+  }
+}
+
 template <class P, class G, bool BATCH>
 __global__ __launch_bounds__((conv_block<P, G, BATCH>()),
                              (conv_block<P, G, BATCH>() == 512 ? (P::fixed ? 4 : 2) : 1)) void
@@ -954,7 +992,7 @@ k_conv(Args a_in, BatchArgs bt) {
   // the first chunk's loads are issued before the tables are computed
   // (when they fit in a few registers)
   constexpr int EPT = (CZ * K2 + NT - 1) / NT;
-  constexpr bool PREFETCH = P::fixed && EPT * sizeof(cplx<T>) <= 32;
+  constexpr bool PREFETCH = EPT * sizeof(cplx<T>) <= 80;
   cplx<T> first[PREFETCH ? EPT : 1];
   if constexpr (PREFETCH) {
 #pragma unroll
@@ -1065,7 +1103,10 @@ k_conv(Args a_in, BatchArgs bt) {
 //   k_conv_z      z transforms, influence function and inverse z transforms
 //                 of a chunk of y-columns of one column (plus the counts
 //                 workgroup)
-//   k_conv_y<+1>  inverse y transforms
+//   k_conv_y<+1>  inverse y transforms (plus, when the energy is wanted, a
+//                 workgroup that adds its partial rows: at 128^3 the
+//                 interpolation's tiles leave no room for it, and it would
+//                 start when the first of them ends)
 // ---------------------------------------------------------------------------
 constexpr int kPassThreads = 256;
 template <class G>
@@ -1105,6 +1146,10 @@ __global__ __launch_bounds__(kPassThreads) void k_conv_y(Args a_in, BatchArgs bt
   cplx<T>* buf = reinterpret_cast<cplx<T>*>(smem);
   cplx<T>* tw = buf + CZ * PY;
   const int tid = threadIdx.x;
+  if (DIR > 0 && blockIdx.x == (K1 / 2 + 1) * NZC) {
+    if (a.reduce_ev) reduce_ev(a, reinterpret_cast<double*>(smem));
+    return;
+  }
   const int xp = blockIdx.x / NZC, z0 = (blockIdx.x - xp * NZC) * CZ;
   const size_t off = ((size_t)xp * K3 + z0) * K2;  // rows [zz][y]
   const In* src = reinterpret_cast<const In*>(a.ws + (DIR < 0 ? a.lay.spec : a.lay.mid)) + off;
@@ -1149,12 +1194,24 @@ __global__ __launch_bounds__(kPassThreads) void k_conv_z(Args a_in, BatchArgs bt
   const int xp = blockIdx.x / NYC, y0 = (blockIdx.x - xp * NYC) * CY;
   cplx<T>* col = reinterpret_cast<cplx<T>*>(a.ws + a.lay.mid) + (size_t)xp * K3 * K2;  // [z][y]
   const cplx<T>* twg = reinterpret_cast<const cplx<T>*>(a.ws + a.lay.tw);
-  for (int i = tid; i < K3 * CY; i += NT) {
-    const int z = i / CY, yy = i - z * CY;
-    buf[z * PZ + yy] = spec_ld(&col[(size_t)z * K2 + y0 + yy]);
+  // every load is issued before the factors are computed
+  constexpr int EPT = K3 * CY / NT;
+  static_assert(K3 * CY % NT == 0, "z pass chunks");
+  cplx<T> first[EPT];
+#pragma unroll
+  for (int k = 0; k < EPT; ++k) {
+    const int i = tid + k * NT, z = i / CY, yy = i - z * CY;
+    first[k] = spec_ld(&col[(size_t)z * K2 + y0 + yy]);
   }
   for (int i = tid; i < K3; i += NT) tw[i] = twg[K1 + K2 + i];
-  axis_factors<G, NT>(a, bs);
+  // the factors of this column and chunk: x' = xp, y0 .. y0+CY-1, every z
+  for (int i = tid; i < 1 + CY + K3; i += NT)
+    axis_factor<G>(a, bs, i == 0 ? xp : i <= CY ? K1 + y0 + i - 1 : K1 + K2 + i - 1 - CY);
+#pragma unroll
+  for (int k = 0; k < EPT; ++k) {
+    const int i = tid + k * NT, z = i / CY, yy = i - z * CY;
+    buf[z * PZ + yy] = first[k];
+  }
   __syncthreads();
   TRACE(4, 1);
   const int yy = tid / TZ, l = tid - yy * TZ;
@@ -1345,25 +1402,6 @@ __global__ __launch_bounds__(conv_reg_threads<G>()) void k_conv_reg(Args a_in, B
   TRACE(2, 15);
 }
 
-// Sum of the energy/virial partial rows the step's convolution variant wrote,
-// in a fixed order, by the first wavefront of the calling workgroup
-// (whatever its size): lane l adds rows l, l+64, ..., then a DPP sum over
-// the lanes.
-static __device__ void reduce_ev(const Args& a) {
-  if (threadIdx.x >= 64) return;
-  const double* partial = reinterpret_cast<const double*>(a.ws + a.lay.partial);
-  double v[7] = {0, 0, 0, 0, 0, 0, 0};
-  for (int r = threadIdx.x; r < a.ev_rows; r += 64) {
-#pragma unroll
-    for (int c = 0; c < 7; ++c) v[c] += partial[r * 8 + c];
-  }
-  wave_sums<7>(v);
-  if (threadIdx.x == 63) {
-#pragma unroll
-    for (int c = 0; c < 7; ++c) a.ev[c] = v[c];
-  }
-}
-
 // ---------------------------------------------------------------------------
 // k_inv_x: complex-to-real x transform of one z-plane into the potential
 // rows of the workspace (with a (p-1)-point wrap halo in front).  Used on
@@ -1371,11 +1409,11 @@ static __device__ void reduce_ev(const Args& a) {
 // ---------------------------------------------------------------------------
 // Row pitch (complex) of the potential rows of k_inv_x and k_interp: the
 // half spectrum X_0 .. X_{K1/2} (odd: the transform takes one row per lane),
-// plus one and widened where the register inverse x transform uses the row
-// itself as its transpose scratch (RX lanes of 9 complex each).
+// widened where the register inverse x transform uses the row itself as its
+// transpose scratch (RX lanes of 9 complex each).
 template <int K1>
 __host__ __device__ constexpr int x_row_pitch() {
-  return !reg_x_ok<K1>() ? K1 / 2 + 1 : (K1 / 16) * 9 > K1 / 2 + 2 ? (K1 / 16) * 9 : K1 / 2 + 2;
+  return reg_x_ok<K1>() ? K1 / 16 * 9 : K1 / 2 + 1;
 }
 template <class P, class G, int ORDER>
 __host__ __device__ constexpr size_t inv_x_lds_bytes() {
@@ -1523,7 +1561,7 @@ __global__ __launch_bounds__(kInterpThreads) void k_interp(Args a_in, BatchArgs 
   TRACE(3, 0);
   const int tid = threadIdx.x;
   if (blockIdx.x == K3 * NQ) {
-    if (a.reduce_ev) reduce_ev(a);
+    if (a.reduce_ev) reduce_ev(a, reinterpret_cast<double*>(smem));
     return;
   }
   if (a.N == 0) return;
@@ -1628,7 +1666,8 @@ __global__ __launch_bounds__(kInterpThreads) void k_interp_phi(Args a_in, BatchA
   __shared__ int nb[4];  // head count, body count, overflow count
   const int tid = threadIdx.x;
   if (blockIdx.x == K3 * NQ) {
-    if (a.reduce_ev) reduce_ev(a);
+    __shared__ double wred[32];
+    if (a.reduce_ev) reduce_ev(a, wred);
     return;
   }
   if (a.N == 0) return;
@@ -1874,8 +1913,8 @@ hipError_t launch_conv_p(const Args& a, hipStream_t s, const Timing& t, const Ba
             e = launch(k_conv_z<P, G, B>, dim3(KH * (G::K2 / pass_cy<G>()) + 1),
                        dim3(kPassThreads), conv_z_lds_bytes<P, G>(), s, Timing(), a, bt);
           if (e == hipSuccess)
-            e = launch(k_conv_y<P, G, 1, B>, ygrid, dim3(kPassThreads), conv_y_lds_bytes<P, G>(),
-                       s, last, a, bt);
+            e = launch(k_conv_y<P, G, 1, B>, dim3(ygrid.x + ((a.reduce_ev || B) ? 1 : 0)), 
+                       dim3(kPassThreads), conv_y_lds_bytes<P, G>(), s, last, a, bt);
           return e;
         }
       } else if (a.conv_mode == kConvFused) {
@@ -1918,7 +1957,9 @@ hipError_t launch_interp_p(const Args& a, hipStream_t s, const Timing& t, const 
       constexpr int O = decltype(oc)::value;
       return with_batch(bt, [&](auto bc) {
         constexpr bool B = decltype(bc)::value;
-        const int blocks = G::K3 * nq_of(G::K2, P::fixed) + ((a.reduce_ev || B) ? 1 : 0);
+        // (the split convolution has summed the energy rows itself)
+        const bool sum_ev = (a.reduce_ev || B) && a.conv_mode != kConvSplit;
+        const int blocks = G::K3 * nq_of(G::K2, P::fixed) + (sum_ev ? 1 : 0);
         if (a.interp_mode == kInterpSplit) {
           // inverse x transform once per plane, then the gather; the timing
           // window spans both launches

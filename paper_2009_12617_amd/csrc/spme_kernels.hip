@@ -8,7 +8,10 @@
 namespace spme {
 
 // Sum of the energy/virial rows by one wavefront (pme_solve outside a step).
-__global__ __launch_bounds__(64) void k_reduce_ev(Args a) { reduce_ev(a); }
+__global__ __launch_bounds__(kReduceThreads) void k_reduce_ev(Args a) {
+  __shared__ double wred[32];
+  reduce_ev(a, wred);
+}
 
 // Clears the bucket and overflow counts of a step whose binning ran without
 // its convolution (one workgroup).
@@ -216,7 +219,7 @@ hipError_t launch_interp(const Args& a, hipStream_t s, const Timing& t, const Ba
 }
 
 hipError_t launch_reduce_ev(const Args& a, hipStream_t s) {
-  k_reduce_ev<<<dim3(1), dim3(64), 0, s>>>(a);
+  k_reduce_ev<<<dim3(1), dim3(kReduceThreads), 0, s>>>(a);
   return hipGetLastError();
 }
 

@@ -60,3 +60,17 @@ def test_fused_column_has_the_bits_of_the_split_passes(P, shape):
         out.append((forces.cpu().numpy(), ev.cpu().numpy()))
     assert np.array_equal(out[0][0], out[1][0])
     assert np.allclose(out[0][1], out[1][1], rtol=1e-12, atol=1e-13 * abs(out[0][1][0]))
+
+
+@pytest.mark.parametrize("shape,conv", [((64,) * 3, 0), ((64,) * 3, 1), ((64,) * 3, 2),
+                                        ((128,) * 3, 1), ((16,) * 3, 0)], ids=str)
+def test_energy_rows_are_summed_once_by_either_call(P, shape, conv):
+    # the same rows in the same order: a step, and solve() on its own
+    plan, pos, q, box = plan_and_inputs(P, shape, "fp32_fixed")
+    plan.set_tuning(conv=conv)
+    _, ev = plan.step(pos, q, box)
+    plan.spread(pos, q, box)
+    alone = plan.solve()
+    forces = plan.gather()
+    assert torch.equal(ev, alone)
+    assert bool(torch.isfinite(forces).all())
