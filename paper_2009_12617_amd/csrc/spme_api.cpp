@@ -375,6 +375,28 @@ int solve_impl(pme_plan* p, double* ev, bool fused) {
   return PME_OK;
 }
 
+// Whether a step may go in one launch: nothing between its stages is asked
+// for (the charge grid, kernel times), and no counts of an unfinished step
+// wait to be cleared.
+bool one_launch_ok(const pme_plan* p, int N) {
+  return p->K1 * p->K2 * p->K3 <= spme::kSmallPoints && N >= 1 && !p->keep_grid && !p->timing &&
+         p->state != kSpread && p->state != kDirty;
+}
+
+// A whole step in one launch (inputs set).
+int small_step(pme_plan* p, double* forces, int accumulate, double* ev) {
+  Args& a = p->cur;
+  a.forces = forces;
+  a.accumulate = accumulate ? 1 : 0;
+  a.ev = ev;
+  a.reduce_ev = ev != nullptr ? 1 : 0;
+  const int rc = device_error(spme::launch_step_small(a, p->stream));
+  a.reduce_ev = 0;
+  p->grid_kept = 0;
+  p->state = rc == PME_OK ? kSolved : kDirty;
+  return rc;
+}
+
 int gather_impl(pme_plan* p, double* forces, int accumulate) {
   if (p->state != kSolved) return PME_ESTATE;
   Args& a = p->cur;
@@ -403,6 +425,11 @@ int pme_step(pme_plan* p, const double* pos, const double* q, int N, const doubl
              double* forces, int accumulate, double* ev) {
   if (p == nullptr) return PME_EINVAL;
   if (N > 0 && forces == nullptr) return PME_EINVAL;
+  if (one_launch_ok(p, N)) {
+    const int rc = set_inputs(p, p->cur, pos, q, N, box);
+    if (rc != PME_OK) return rc;
+    if (spme::step_small_wins(p->cur)) return small_step(p, forces, accumulate, ev);
+  }
   int rc = pme_spread(p, pos, q, N, box);
   if (rc == PME_OK) rc = solve_impl(p, ev, true);
   if (rc == PME_OK) rc = gather_impl(p, forces, accumulate);

@@ -85,6 +85,17 @@ __device__ __forceinline__ void row_scan_add(double* v) {
   for (int c = 0; c < V; ++c) v[c] += dpp_f64<0x118, 0xf>(v[c]);
 }
 
+// Inclusive prefix sums over the first 32 lanes of the wavefront (DPP row
+// scans, then the first row's sum into the second).
+__device__ __forceinline__ int scan32_add(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);  // row_shr 1
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0x2, 0xf, false);  // row_bcast 15
+  return v;
+}
+
 // wave_sums: an inclusive DPP scan of V doubles over the wavefront (rows,
 // then row_bcast 15 and 31); lane 63 ends with the wavefront's sums.
 // block_sums: sums over the block in a fixed order -- wave_sums, then the
@@ -335,14 +346,14 @@ __device__ __forceinline__ void fft_reg_stages(cplx<T>* v, int j, const cplx<T>*
 }
 
 // In-place N-point transforms of NPEN pencils (element k of pencil p at
-// buf[p * pstride + k * estride]) by a workgroup of NT threads.  read(p, k)
-// gives the elements phase one starts from (the buffer's own, or what a caller
-// forms from them).  Neighbouring lanes take neighbouring pencils: without
-// bank conflicts for pstride 1 or odd.  All threads call it; it synchronises
-// before its first write and at its end, not before its first read.
-template <typename T, int N, int S, int NPEN, int NT, class Read>
-__device__ __forceinline__ void block_fft(cplx<T>* buf, int pstride, int estride, const cplx<T>* tw,
-                                          int twstep, Read&& read) {
+// buf[at(p, k)]) by a workgroup of NT threads.  read(p, k) gives the elements
+// phase one starts from (the buffer's own, or what a caller forms from them).
+// Neighbouring lanes take neighbouring pencils.  All threads call it; it
+// synchronises before its first write and at its end, not before its first
+// read.
+template <typename T, int N, int S, int NPEN, int NT, class At, class Read>
+__device__ __forceinline__ void block_fft_at(cplx<T>* buf, At&& at, const cplx<T>* tw, int twstep,
+                                             Read&& read) {
   constexpr int N1 = fft_n1(N), N2 = fft_n2(N), SPLIT = fft_split(N), NS = fft_nstages(N);
   constexpr int T1 = NPEN * N2, TPT = (T1 + NT - 1) / NT, T2 = NPEN * N1;
   const int tid = threadIdx.x;
@@ -364,7 +375,7 @@ __device__ __forceinline__ void block_fft(cplx<T>* buf, int pstride, int estride
     if (T1 % NT == 0 || task < T1) {
       const int p = task % NPEN, m = task / NPEN;
 #pragma unroll
-      for (int j = 0; j < N1; ++j) buf[p * pstride + (m * N1 + j) * estride] = v[i][j];
+      for (int j = 0; j < N1; ++j) buf[at(p, m * N1 + j)] = v[i][j];
     }
   }
   __syncthreads();
@@ -372,12 +383,20 @@ __device__ __forceinline__ void block_fft(cplx<T>* buf, int pstride, int estride
     const int p = task % NPEN, j = task / NPEN;
     cplx<T> w[N2];
 #pragma unroll
-    for (int m = 0; m < N2; ++m) w[m] = buf[p * pstride + (m * N1 + j) * estride];
+    for (int m = 0; m < N2; ++m) w[m] = buf[at(p, m * N1 + j)];
     fft_reg_stages<T, N, S, SPLIT, NS, N2>(w, j, tw, twstep);
 #pragma unroll
-    for (int t = 0; t < N2; ++t) buf[p * pstride + (j + N1 * t) * estride] = w[t];
+    for (int t = 0; t < N2; ++t) buf[at(p, j + N1 * t)] = w[t];
   }
   __syncthreads();
+}
+// ... with element k of pencil p at buf[p pstride + k estride]: without bank
+// conflicts for pstride 1 or odd.
+template <typename T, int N, int S, int NPEN, int NT, class Read>
+__device__ __forceinline__ void block_fft(cplx<T>* buf, int pstride, int estride, const cplx<T>* tw,
+                                          int twstep, Read&& read) {
+  block_fft_at<T, N, S, NPEN, NT>(
+      buf, [&](int p, int k) { return p * pstride + k * estride; }, tw, twstep, read);
 }
 template <typename T, int N, int S, int NPEN, int NT>
 __device__ __forceinline__ void block_fft(cplx<T>* buf, int pstride, int estride, const cplx<T>* tw,
@@ -395,7 +414,7 @@ __device__ __forceinline__ void block_fft(cplx<T>* buf, int pstride, int estride
 // ---------------------------------------------------------------------------
 // Modes k and M - k of the row from Z_k and Z_{M-k} (k = 0: modes 0 and M).
 template <typename T, int N, class Sink>
-__device__ __forceinline__ void r2c_pair(int k, const cplx<T>& zk, const cplx<T>& zm,
+__device__ __forceinline__ void r2c_pair(int k, cplx<T> zk, cplx<T> zm,
                                          const cplx<T>* twN, Sink&& sink) {
   constexpr int M = N / 2;
   cplx<T> e = c_scale(c_add(zk, c_conj(zm)), T(0.5));

@@ -16,6 +16,7 @@ constexpr int kMaxBins = 2048;       // (z, y slice, head/body) bins: 2 K3 nq <=
 constexpr int kSpreadThreads = 1024, kSpreadThreadsBatch = 512;
 constexpr int kPlaneThreads = 512;   // one z-plane per workgroup (debug potential copy)
 constexpr int kInterpThreads = 512;  // one (z-plane, y slice) bin per workgroup
+constexpr int kSmallPoints = 16 * 16 * 16;  // largest grid of the one-launch step
 constexpr int kMaxLds = 160 * 1024;  // LDS per workgroup on gfx950
 constexpr int kNumKernels = 4;       // bin, spread+x, yz convolution, inverse x + interpolation
 
@@ -134,6 +135,7 @@ struct PrecOps {
   hipError_t (*prepare)(int K1, int K2, int K3, int order);  // dynamic-LDS limits
   unsigned (*variants)(int K1, int K2, int K3, int order);   // kVar* bits
   LaunchFn bin, spread_x, conv, inv_x, interp;
+  LaunchFn step_small;  // the whole step of a small system, one launch
 #ifdef SPME_TRACE
   hipError_t (*trace_set)(void* buf);
 #endif
@@ -163,6 +165,19 @@ hipError_t launch_conv(const Args& a, hipStream_t s, const Timing& t = Timing(),
 hipError_t launch_reduce_ev(const Args& a, hipStream_t s);
 hipError_t launch_inv_x(const Args& a, hipStream_t s, const Timing& t = Timing(),
                         const BatchArgs* bt = nullptr);
+// Whether one workgroup does the step of these inputs faster than the chain of
+// launches.  Measured at 16^3 (one launch / four, us): the grid and its
+// transforms cost the one workgroup 12 to 13 us (FP64 14, a general cell 4
+// more) and each of the N p^3 contributions its share of one CU's LDS atomics
+// --  p = 4: 64 atoms 12.8 / 17.8, 320 15.0 / 18.2, 576 17.4 / 18.7, 768
+//     18.5 / 18.9, 1024 20.3 / 19.2;  p = 6: 256 19.8 / 21.2, 320 22.0 / 21.6
+//     FP64: p = 4: 320 17.9 / 19.0, 448 19.3 / 19.3;  p = 6: 128 20.8 / 21.4,
+//     192 23.6 / 21.7
+//     general cell: p = 4: 320 19.4 / 19.5, 448 20.3 / 19.8; FP64 p = 4: 128
+//     19.3 / 19.6, 192 20.3 / 20.0
+// -- so the line is drawn on N p^2.  (24^3 lost at every size: 25 / 19.)
+bool step_small_wins(const Args& a);
+hipError_t launch_step_small(const Args& a, hipStream_t s);
 hipError_t launch_interp(const Args& a, hipStream_t s, const Timing& t = Timing(),
                          const BatchArgs* bt = nullptr);
 hipError_t launch_clear_counts(const Args& a, hipStream_t s);

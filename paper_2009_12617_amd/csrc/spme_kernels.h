@@ -101,6 +101,14 @@ __device__ __forceinline__ void spec_st(cplx_b* p, cplx<float> v) {
   *p = cplx_b{bf16_rne(v.x), bf16_rne(v.y)};
 }
 
+// A value as it comes back from the stored format.
+template <class S, typename T>
+__device__ __forceinline__ cplx<T> spec_round(cplx<T> v) {
+  S s;
+  spec_st(&s, v);
+  return spec_ld(&s);
+}
+
 struct PFixed {
   using real = float;
   using acc = unsigned long long;
@@ -169,6 +177,45 @@ __device__ __forceinline__ T pick(const T* a, int i) {
   return v;
 }
 
+// The record of atom i and its base grid point g.  Returns the atom's |q|; an
+// atom with a coordinate or charge that is not finite contributes nothing and
+// is reported through the sticky flags (once: report).
+template <class P>
+__device__ __forceinline__ double make_record(const Args& a, int i, bool report,
+                                              typename P::rec& r, int* g) {
+  using T = typename P::real;
+  double w[3];
+  bool ok = true;
+  const double x3[3] = {a.pos[3 * (size_t)i], a.pos[3 * (size_t)i + 1], a.pos[3 * (size_t)i + 2]};
+  if (!a.triclinic) {
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+      const int Kd = d == 0 ? a.K1 : d == 1 ? a.K2 : a.K3;
+      ok &= grid_coord(x3[d], a.invL[d], Kd, &g[d], &w[d]);
+    }
+  } else {
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+      const int Kd = d == 0 ? a.K1 : d == 1 ? a.K2 : a.K3;
+      ok &= grid_coord_s(frac_general(x3, a.rec + 3 * d), Kd, &g[d], &w[d]);
+    }
+  }
+  double qi = a.q[i];
+  ok &= (qi - qi == 0.0);  // finite
+  if (!ok) {
+    qi = 0.0;
+    if (report) atomicOr(reinterpret_cast<unsigned*>(a.ws + a.lay.ctrl), PME_FLAG_NONFINITE);
+  }
+  r.g = g[0] | (g[1] << 10) | (g[2] << 20);
+  r.w[0] = (T)w[0];
+  r.w[1] = (T)w[1];
+  r.w[2] = (T)w[2];
+  r.q = (T)qi;
+  r.qd = qi;
+  r.idx = i;
+  return fabs(qi);
+}
+
 // ---------------------------------------------------------------------------
 // k_bin: one chunk of atoms per workgroup (the plan's binning chunk, 256 to
 // 1024 atoms), one atom per thread.  Each
@@ -185,7 +232,6 @@ __global__ __launch_bounds__(kBinThreads) void k_bin(Args a_in, BatchArgs bt) {
   const Args a = BATCH ? *bt.sys[blockIdx.y] : a_in;
   if (BATCH && (int)blockIdx.x >= a.n_chunks) return;
   using Rec = typename P::rec;
-  using T = typename P::real;
   __shared__ int hist[kMaxBins];
   __shared__ double wred[16 * 8];
   TRACE(0, 0);
@@ -208,36 +254,7 @@ __global__ __launch_bounds__(kBinThreads) void k_bin(Args a_in, BatchArgs bt) {
   double v[1] = {0.0};
   if (i < a.N) {
     int g[3];
-    double w[3];
-    bool ok = true;
-    const double x3[3] = {a.pos[3 * (size_t)i], a.pos[3 * (size_t)i + 1], a.pos[3 * (size_t)i + 2]};
-    if (!a.triclinic) {
-#pragma unroll
-      for (int d = 0; d < 3; ++d) {
-        const int Kd = d == 0 ? a.K1 : d == 1 ? a.K2 : a.K3;
-        ok &= grid_coord(x3[d], a.invL[d], Kd, &g[d], &w[d]);
-      }
-    } else {
-#pragma unroll
-      for (int d = 0; d < 3; ++d) {
-        const int Kd = d == 0 ? a.K1 : d == 1 ? a.K2 : a.K3;
-        ok &= grid_coord_s(frac_general(x3, a.rec + 3 * d), Kd, &g[d], &w[d]);
-      }
-    }
-    double qi = a.q[i];
-    ok &= (qi - qi == 0.0);  // finite
-    if (!ok) {
-      qi = 0.0;  // contributes nothing; reported through the sticky flag
-      atomicOr(flags, PME_FLAG_NONFINITE);
-    }
-    v[0] = fabs(qi);
-    r.g = g[0] | (g[1] << 10) | (g[2] << 20);
-    r.w[0] = (T)w[0];
-    r.w[1] = (T)w[1];
-    r.w[2] = (T)w[2];
-    r.q = (T)qi;
-    r.qd = qi;
-    r.idx = i;
+    v[0] = make_record<P>(a, i, true, r, g);
     // bin (z, y slice, head/body): the head holds the atoms whose support
     // also reaches the slice below (g_y mod rows < p - 1)
     const int sl = g[1] / rows;
@@ -514,12 +531,7 @@ __global__ __launch_bounds__(spread_threads<BATCH>()) void k_spread_x(Args a_in,
       bk_end[NBK] = (int)min(reinterpret_cast<const unsigned*>(a.ws + a.lay.ovf)[0],
                              (unsigned)a.lay.orec_max);
     }
-    int end = n;  // the items of the buckets one after another
-#pragma unroll
-    for (int d = 1; d < NBK; d *= 2) {
-      const int below = __shfl_up(end, d);
-      end += tid >= d ? below : 0;
-    }
+    const int end = scan32_add(n);  // the items of the buckets one after another
     if (tid < NBK) {
       bk_end[tid] = end;
       bk_off[tid] = b * cap - (end - n);
@@ -1785,6 +1797,199 @@ hipError_t with_batch(const BatchArgs* bt, F&& f) {
   return f(std::false_type{});
 }
 
+// ---------------------------------------------------------------------------
+// k_step_small: a whole step on a 16^3 grid by one workgroup, the grid and its
+// half spectrum in LDS from the first contribution to the last force.  At this
+// size each of the step's four launches is a chain of latencies -- launch,
+// arguments, counts, records, stores -- around a few hundred nanoseconds of
+// work.  192 atoms, p = 4: 18.2 -> 13.5 us, of which loads and tables 1.4,
+// spreading 2.4 (LDS atomics), transforms 5.4, influence function 2.2 (FP64
+// rate of one CU), interpolation 1.5, energy 0.9.  The arithmetic is that of the separate kernels (the same splines,
+// butterflies, influence function and, between the stages, the same rounding
+// to the stored spectrum format).  The records, the counts and the spectrum
+// are also left in the workspace, so that a gather or a debug copy may follow.
+// ---------------------------------------------------------------------------
+constexpr int kSmallThreads = 1024;
+template <class G>
+__host__ __device__ constexpr bool step_small_shape() {
+  return G::K1 * G::K2 * G::K3 <= kSmallPoints;
+}
+template <class P, class G>
+__host__ __device__ constexpr size_t step_small_lds_bytes() {
+  return (size_t)G::K2 * G::K3 * tile_pitch<P>(G::K1) * 8 +
+         (size_t)(G::K1 + G::K2 + G::K3) * (sizeof(cplx<typename P::real>) + sizeof(double)) +
+         16 * 8 * sizeof(double) + (2 * G::K3 * nq_of(G::K2, P::fixed) + 2) * sizeof(int);
+}
+
+template <class P, class G, int ORDER>
+__global__ __launch_bounds__(kSmallThreads) void k_step_small(Args a) {
+  using T = typename P::real;
+  using Acc = typename P::acc;
+  using Rec = typename P::rec;
+  using S = typename P::spec;
+  constexpr int K1 = G::K1, K2 = G::K2, K3 = G::K3, M = K1 / 2, KH = M + 1;
+  constexpr int NT = kSmallThreads, NROW = K2 * K3;
+  constexpr int PITCH = tile_pitch<P>(K1), PC = P::fixed ? PITCH : PITCH / 2;
+  constexpr int NQ = nq_of(K2, P::fixed), R = K2 / NQ, NBINS = 2 * K3 * NQ;
+  static_assert(PC >= KH && step_small_lds_bytes<P, G>() <= kMaxLds, "grid in LDS");
+  extern __shared__ __align__(16) unsigned char smem[];
+  Acc* tile = reinterpret_cast<Acc*>(smem);              // rows [z][y] of x
+  cplx<T>* rows = reinterpret_cast<cplx<T>*>(smem);      // the same rows, transformed
+  cplx<T>* tw = reinterpret_cast<cplx<T>*>(smem + (size_t)NROW * PITCH * 8);
+  double* bs = reinterpret_cast<double*>(tw + K1 + K2 + K3);  // x, y, z factors
+  double* wred = bs + K1 + K2 + K3;
+  int* hist = reinterpret_cast<int*>(wred + 16 * 8);     // [NBINS] counts, overflow count
+  const int tid = threadIdx.x;
+  TRACE(2, 0);
+
+  // atom tid % NA, NA the atoms rounded up to whole wavefronts; the planes of
+  // its support are dealt to the thread groups that fit, and a group more (the
+  // first, where there is none) puts its record into its bucket
+  const int NA = (a.N + 63) & ~63;
+  const int rep = tid / NA, nrep = min(NT / NA, ORDER), atom = tid - rep * NA;
+  const int brep = NT / NA > ORDER ? ORDER : 0;
+  const bool owns = rep == 0 && atom < a.N, bins = rep == brep && atom < a.N;
+  const bool spreads = rep < nrep && atom < a.N;
+  Rec r;
+  int g[3] = {0, 0, 0};
+  double v[1] = {0.0};
+  if (spreads || bins) {
+    const double aq = make_record<P>(a, atom, owns, r, g);
+    if (owns) v[0] = aq;
+  }
+  const cplx<T>* twg = reinterpret_cast<const cplx<T>*>(a.ws + a.lay.tw);
+  for (int i = tid; i < K1 + K2 + K3; i += NT) tw[i] = twg[i];
+  axis_factors<G, NT>(a, bs);
+  for (int i = tid; i < NROW * PITCH; i += NT) tile[i] = Acc(0);
+  if (tid <= NBINS) hist[tid] = 0;
+  static_assert(NBINS < NT, "one thread per bin");
+  __syncthreads();
+  TRACE(2, 1);
+
+  // the atom's place in its bucket, for a later gather
+  if (bins) {
+    const int sl = g[1] / R, cap = a.lay.cap;
+    const int bin = (g[2] * NQ + sl) * 2 + ((g[1] - sl * R) >= ORDER - 1 ? 1 : 0);
+    const int slot = atomicAdd(&hist[bin], 1);
+    if (slot < cap) {
+      reinterpret_cast<Rec*>(a.ws + a.lay.rec)[(size_t)bin * cap + slot] = r;
+    } else {
+      const int o = atomicAdd(&hist[NBINS], 1);  // (at most N <= orec_max)
+      reinterpret_cast<Rec*>(a.ws + a.lay.orec)[o] = r;
+    }
+  }
+  const double scale = ldexp(1.0, a.frac_bits);
+  if (spreads) {
+    for (int jz = rep; jz < ORDER; jz += nrep) {
+      int z = g[2] - ORDER + 1 + jz;
+      if (z < 0) z += K3;
+      spread_atom<P, K1, K2, ORDER, K2, PITCH>(tile + z * K2 * PITCH, r, jz, 0, scale);
+    }
+  }
+  block_sums<1>(v, wred);  // (its barrier completes the counts)
+  if (P::fixed && tid == 15 && v[0] * scale >= 2251799813685248.0)
+    atomicOr(reinterpret_cast<unsigned*>(a.ws + a.lay.ctrl), PME_FLAG_OVERFLOW);
+  if (tid < NBINS) reinterpret_cast<unsigned*>(a.ws + a.lay.bcnt2)[tid] = (unsigned)hist[tid];
+  if (tid == NBINS) reinterpret_cast<unsigned*>(a.ws + a.lay.ovf)[1] = (unsigned)hist[NBINS];
+  __syncthreads();
+  TRACE(2, 2);
+
+  // x, real-to-complex, in place: X_k of a row at its element k
+  if constexpr (P::fixed) {
+    const double inv_scale = ldexp(1.0, -a.frac_bits);
+    block_fft<T, M, -1, NROW, NT>(rows, PC, 1, tw, 2, [&](int y, int n) -> cplx<T> {
+      const Acc* ri = tile + y * PITCH;
+      return {(float)((double)(long long)ri[2 * n] * inv_scale),
+              (float)((double)(long long)ri[2 * n + 1] * inv_scale)};
+    });
+  } else {
+    block_fft<T, M, -1, NROW, NT>(rows, PC, 1, tw, 2);
+  }
+  for (int i = tid; i < NROW * (M / 2 + 1); i += NT) {
+    const int k = i / NROW;
+    cplx<T>* row = rows + (i - k * NROW) * PC;
+    r2c_pair<T, K1>(k, row[k], row[(M - k) % M], tw,
+                    [&](int x, const cplx<T>& w) { row[x] = spec_round<S>(w); });
+  }
+  __syncthreads();
+  TRACE(2, 3);
+
+  // y, z, influence function, z, y; a pencil per (x', z) and per (x', y)
+  const cplx<T>* twy = tw + K1;
+  const cplx<T>* twz = twy + K2;
+  auto aty = [](int p, int k) { return (p / KH * K2 + k) * PC + p % KH; };
+  auto atz = [](int p, int k) { return (k * K2 + p / KH) * PC + p % KH; };
+  auto ldy = [&](int p, int k) { return rows[aty(p, k)]; };
+  auto ldz = [&](int p, int k) { return rows[atz(p, k)]; };
+  block_fft_at<T, K2, -1, KH * K3, NT>(rows, aty, twy, 1, ldy);
+  block_fft_at<T, K3, -1, KH * K2, NT>(rows, atz, twz, 1, ldz);
+  TRACE(2, 4);
+  // (by the last 12 wavefronts: the first four then interpolate, up to 256
+  // atoms, while the others add up their energy and virial)
+  constexpr int VT0 = 256;
+  double acc[7] = {0, 0, 0, 0, 0, 0, 0};
+  for (int i = tid - VT0; i >= 0 && i < KH * NROW; i += NT - VT0) {
+    const int row = i / KH, xp = i - row * KH, z = row / K2, y = row - z * K2;
+    const InflCol c = infl_col<G>(a, xp, bs);
+    cplx<T>& f = rows[row * PC + xp];
+    f = a.triclinic ? infl_general<G>(a, c, xp, y, z, bs, f, acc)
+                    : infl_ortho<G>(a, c, xp, y, z, bs, f, acc);
+  }
+  __syncthreads();
+  TRACE(2, 5);
+  block_fft_at<T, K3, 1, KH * K2, NT>(rows, atz, twz, 1, ldz);
+  block_fft_at<T, K2, 1, KH * K3, NT>(rows, aty, twy, 1, ldy);
+  TRACE(2, 6);
+  S* spec = reinterpret_cast<S*>(a.ws + a.lay.spec);  // columns [x'][z][y]
+  for (int i = tid; i < KH * NROW; i += NT) {
+    const int xp = i / NROW, row = i - xp * NROW;
+    spec_st(&spec[i], rows[row * PC + xp]);
+  }
+  // x, complex-to-real: the potential
+  block_fft<T, M, 1, NROW, NT>(rows, PC, 1, tw, 2, [&](int row, int k) {
+    return c2r_mode(k, spec_round<S>(rows[row * PC + k]), spec_round<S>(rows[row * PC + M - k]), tw);
+  });
+
+  TRACE(2, 7);
+  if (owns) {
+    int xs[ORDER];
+#pragma unroll
+    for (int jx = 0; jx < ORDER; ++jx) {
+      const int x = g[0] - ORDER + 1 + jx;
+      xs[jx] = x < 0 ? x + K1 : x;
+    }
+    interpolate<P, ORDER>(
+        a, r,
+        [&](int jz, int jy) {
+          int z = g[2] - ORDER + 1 + jz, y = g[1] - ORDER + 1 + jy;
+          if (z < 0) z += K3;
+          if (y < 0) y += K2;
+          return reinterpret_cast<const T*>(rows + (z * K2 + y) * PC);
+        },
+        xs);
+  }
+  TRACE(2, 8);
+  if (!a.reduce_ev) return;
+  if (tid >= VT0) {
+    wave_sums<7>(acc);
+    if ((tid & 63) == 63) {
+#pragma unroll
+      for (int c = 0; c < 7; ++c) wred[(tid >> 6) * 8 + c] = acc[c];
+    }
+  }
+  __syncthreads();
+  if (tid < 7) {
+    double s = 0.0, e = 0.0;
+#pragma unroll
+    for (int w = VT0 / 64; w < NT / 64; ++w) {
+      e += wred[w * 8];
+      s += wred[w * 8 + tid];
+    }
+    a.ev[tid] = tid == 0 ? e : tid < 4 ? e - 2.0 * s : -2.0 * s;
+  }
+  TRACE(2, 15);
+}
+
 // Which variants of the convolution and interpolation a (precision, grid,
 // order) combination can run: the fused column must fit in LDS, the split
 // passes need whole chunks of rows per workgroup, the fused interpolation
@@ -1839,6 +2044,11 @@ hipError_t raise_all_lds_limits() {
     if (e == hipSuccess)
       e = hipFuncSetAttribute((const void*)k_interp<P, G, O, B>, attr,
                               (int)interp_lds_bytes<P, G, O>());
+  }
+  if constexpr (step_small_shape<G>() && !B) {
+    if (e == hipSuccess)
+      e = hipFuncSetAttribute((const void*)k_step_small<P, G, O>, attr,
+                              (int)step_small_lds_bytes<P, G>());
   }
   return e;
 }
@@ -1982,6 +2192,22 @@ hipError_t launch_interp_p(const Args& a, hipStream_t s, const Timing& t, const 
   });
 }
 
+template <class P>
+hipError_t launch_step_small_p(const Args& a, hipStream_t s, const Timing&, const BatchArgs*) {
+  return with_grid(a.K1, a.K2, a.K3, [&](auto gc) {
+    using G = decltype(gc);
+    return with_order(a.order, [&](auto oc) {
+      constexpr int O = decltype(oc)::value;
+      if constexpr (step_small_shape<G>()) {
+        k_step_small<P, G, O><<<dim3(1), dim3(kSmallThreads), step_small_lds_bytes<P, G>(), s>>>(a);
+        return hipGetLastError();
+      } else {
+        return hipErrorInvalidValue;
+      }
+    });
+  });
+}
+
 // The launch table of one precision (each precision's kernels are compiled
 // in a translation unit of their own).
 template <class P>
@@ -1994,6 +2220,7 @@ PrecOps make_ops() {
   o.conv = &launch_conv_p<P>;
   o.inv_x = &launch_inv_x_p<P>;
   o.interp = &launch_interp_p<P>;
+  o.step_small = &launch_step_small_p<P>;
 #ifdef SPME_TRACE
   o.trace_set = &trace_set_here;
 #endif

@@ -218,6 +218,16 @@ hipError_t launch_interp(const Args& a, hipStream_t s, const Timing& t, const Ba
   return ops == nullptr ? hipErrorInvalidValue : ops->interp(a, s, t, bt);
 }
 
+bool step_small_wins(const Args& a) {
+  const int limit = a.precision != PME_FP64 ? (a.triclinic ? 5120 : 9216)
+                                            : (a.triclinic ? 2048 : 5120);
+  return (long long)a.N * a.order * a.order <= limit;
+}
+hipError_t launch_step_small(const Args& a, hipStream_t s) {
+  const PrecOps* ops = prec_ops(a.precision);
+  return ops == nullptr ? hipErrorInvalidValue : ops->step_small(a, s, Timing(), nullptr);
+}
+
 hipError_t launch_reduce_ev(const Args& a, hipStream_t s) {
   k_reduce_ev<<<dim3(1), dim3(kReduceThreads), 0, s>>>(a);
   return hipGetLastError();
