@@ -1361,20 +1361,24 @@ __global__ __launch_bounds__(conv_reg_threads<G>()) void k_conv_reg(Args a_in, B
       const int my = (2 * y <= K2) ? y : y - K2;
       const double mvy = my * a.invL[1], ny = (2 * y == K2) ? 0.0 : mvy;
       const double Ay = c.A * bs[K1 + y], base = fma(mvy, mvy, c.mvx2);
+      // (bounds of the lane's k-th mode are known at compile time: m = 0 is the
+      // first, a Nyquist index one with z0 <= K3/2; the column's weight of
+      // 1/2 or 1 multiplies the sums)
       double s0 = 0.0, su = 0.0, sz = 0.0, szz = 0.0;
 #pragma unroll
       for (int k = 0; k < 8; ++k) {
-        const int z = j * EZ + k / RZ + 8 * (k % RZ);
-        const int mz = (2 * z <= K3) ? z : z - K3;
-        const double mvz = mz * a.invL[2], nz = (2 * z == K3) ? 0.0 : mvz;
-        const bool m0 = (xp == 0) && (y == 0) && (z == 0);
+        const int z0 = k / RZ + 8 * (k % RZ), z1 = z0 + (RZ - 1) * EZ, z = j * EZ + z0;
+        const int mz = 2 * z1 <= K3 ? z : 2 * z0 > K3 ? z - K3 : (2 * z <= K3) ? z : z - K3;
+        const double mvz = mz * a.invL[2];
+        const double nz = (2 * z0 <= K3 && 2 * z1 >= K3 && 2 * z == K3) ? 0.0 : mvz;
+        const bool m0 = k == 0 && (xp == 0) && (y == 0) && (z == 0);
         const double msq = m0 ? 1.0 : fma(mvz, mvz, base);
         double r = __builtin_amdgcn_rcp(msq);
         r = fma(r, fma(-msq, r, 1.0), r);
         r = fma(r, fma(-msq, r, 1.0), r);
         const double gm = m0 ? 0.0 : Ay * bs[K1 + K2 + z] * r;  // G(m)
         const double f2 = fma((double)v[k].x, (double)v[k].x, (double)v[k].y * (double)v[k].y);
-        const double e = c.wx * gm * f2;
+        const double e = gm * f2;
         const double eu = e * (r + c.fac);
         s0 += e;
         su += eu;
@@ -1383,6 +1387,10 @@ __global__ __launch_bounds__(conv_reg_threads<G>()) void k_conv_reg(Args a_in, B
         const T g = (T)gm;
         v[k] = {v[k].x * g, v[k].y * g};
       }
+      s0 *= c.wx;
+      su *= c.wx;
+      sz *= c.wx;
+      szz *= c.wx;
       acc[0] = s0;
       acc[1] = c.mvx2 * su;
       acc[2] = (mvy * mvy) * su;
