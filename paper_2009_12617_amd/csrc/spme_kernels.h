@@ -815,14 +815,17 @@ __device__ __forceinline__ InflCol infl_col(const Args& a, int xp, const double*
   return c;
 }
 
-// One mode (xp, y, z) of an orthorhombic cell: returns G(m) F(m) and adds
-// the mode's energy/virial terms to acc.
-template <class G, typename T>
-__device__ __forceinline__ cplx<T> infl_ortho(const Args& a, const InflCol& c, int xp, int y,
-                                              int z, const double* bs, cplx<T> f, double* acc) {
+// The modes (xp, +-y, +-z) of an orthorhombic cell, 0 <= y <= K2/2 (YPAIR;
+// without it the modes (xp, y, +-z), any y) and 0 <= z <= K3/2: four modes of
+// one |m|^2 (two or one where an index is 0 or Nyquist).  The reciprocal,
+// 1/|m|^2 + fac and the products of indices are formed once, and the modes'
+// energies enter the sums through their even and odd combinations.  at(y, z):
+// the mode's element.
+template <class G, bool YPAIR, class At>
+__device__ __forceinline__ void infl_mirror(const Args& a, const InflCol& c, int xp, int y, int z,
+                                            const double* bs, At&& at, double* acc) {
   constexpr int K1 = G::K1, K2 = G::K2, K3 = G::K3;
-  const int my = (2 * y <= K2) ? y : y - K2, mz = (2 * z <= K3) ? z : z - K3;
-  const double mvy = my * a.invL[1], mvz = mz * a.invL[2];
+  const double mvy = (2 * y <= K2 ? y : y - K2) * a.invL[1], mvz = z * a.invL[2];
   const double ny = (2 * y == K2) ? 0.0 : mvy, nz = (2 * z == K3) ? 0.0 : mvz;
   // m = 0 carries no energy (G(0) = 0): its |m|^2 is replaced by 1 and its
   // G by 0, without a branch
@@ -832,35 +835,55 @@ __device__ __forceinline__ cplx<T> infl_ortho(const Args& a, const InflCol& c, i
   double r = __builtin_amdgcn_rcp(msq);
   r = fma(r, fma(-msq, r, 1.0), r);
   r = fma(r, fma(-msq, r, 1.0), r);
-  const double gm = m0 ? 0.0 : c.A * bs[K1 + y] * bs[K1 + K2 + z] * r;  // G(m)
-  const double f2 = fma((double)f.x, (double)f.x, (double)f.y * (double)f.y);
-  const double e = c.wx * gm * f2;
-  const double eu = e * (r + c.fac);
-  const double eux = eu * c.mvx, euy = eu * mvy, eun = eu * c.nx;
-  acc[0] += e;
-  acc[1] = fma(eux, c.mvx, acc[1]);
-  acc[2] = fma(euy, mvy, acc[2]);
-  acc[3] = fma(eu * mvz, mvz, acc[3]);
-  acc[4] = fma(eun, ny, acc[4]);
-  acc[5] = fma(eun, nz, acc[5]);
-  acc[6] = fma(eu * ny, nz, acc[6]);
-  const T g = (T)gm;
-  return {f.x * g, f.y * g};
+  const bool two_y = YPAIR && y != 0 && 2 * y != K2, two_z = z != 0 && 2 * z != K3;
+  double e[2][2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      e[i][j] = 0.0;
+      if ((i == 0 || two_y) && (j == 0 || two_z)) {
+        const int yi = i == 0 ? y : K2 - y, zj = j == 0 ? z : K3 - z;
+        const double gm = m0 ? 0.0 : c.A * bs[K1 + yi] * bs[K1 + K2 + zj] * r;  // G(m)
+        auto& f = at(yi, zj);
+        const double f2 = fma((double)f.x, (double)f.x, (double)f.y * (double)f.y);
+        e[i][j] = gm * f2;
+        const auto g = (decltype(f.x + f.x))gm;
+        f.x *= g;
+        f.y *= g;
+      }
+    }
+  const double p0 = e[0][0] + e[0][1], q0 = e[0][0] - e[0][1];
+  const double p1 = e[1][0] + e[1][1], q1 = e[1][0] - e[1][1];
+  const double s = p0 + p1, uw = c.wx * (r + c.fac), us = uw * s;
+  acc[0] = fma(c.wx, s, acc[0]);
+  acc[1] = fma(us, c.mvx2, acc[1]);
+  acc[2] = fma(us * mvy, mvy, acc[2]);
+  acc[3] = fma(us * mvz, mvz, acc[3]);
+  acc[4] = fma(uw * (p0 - p1), c.nx * ny, acc[4]);
+  acc[5] = fma(uw * (q0 + q1), c.nx * nz, acc[5]);
+  acc[6] = fma(uw * (q0 - q1), ny * nz, acc[6]);
 }
 
-// One mode of a general cell: m = m1 a*_1 + m2 a*_2 + m3 a*_3 does not
-// separate; each Nyquist index is averaged over its two signs explicitly.
+// One mode of a general cell, or (pair) the modes of indices m and -m of a
+// column with m1 = -m1, which share |m|^2 and every product: m = m1 a*_1 +
+// m2 a*_2 + m3 a*_3 does not separate; each Nyquist index is averaged over its
+// two signs explicitly.  fb: the element of -m (the same as fa without one).
 template <class G, typename T>
-__device__ __forceinline__ cplx<T> infl_general(const Args& a, const InflCol& c, int xp, int y,
-                                                int z, const double* bs, cplx<T> f, double* acc) {
+__device__ __forceinline__ void infl_general(const Args& a, const InflCol& c, int xp, int y, int z,
+                                             const double* bs, cplx<T>& fa, cplx<T>& fb, bool pair,
+                                             double* acc) {
   constexpr int K1 = G::K1, K2 = G::K2, K3 = G::K3;
   const int ms0[3] = {xp, (2 * y <= K2) ? y : y - K2, (2 * z <= K3) ? z : z - K3};
   const int ny3[3] = {2 * xp == K1, 2 * y == K2, 2 * z == K3};
   const int nvar = 1 << (ny3[0] + ny3[1] + ny3[2]);
-  const double f2 = fma((double)f.x, (double)f.x, (double)f.y * (double)f.y);
-  double gm = 0.0;  // G(m), averaged over the Nyquist signs
+  const cplx<T> va = fa, vb = fb;
+  const double f2a = fma((double)va.x, (double)va.x, (double)va.y * (double)va.y);
+  const double f2b = pair ? fma((double)vb.x, (double)vb.x, (double)vb.y * (double)vb.y) : 0.0;
+  double ga = 0.0, gb = 0.0;  // G(m), averaged over the Nyquist signs
   if (xp != 0 || y != 0 || z != 0) {
-    const double Bw = c.A * bs[K1 + y] * bs[K1 + K2 + z] / nvar;
+    const double Ba = c.A * bs[K1 + y] * bs[K1 + K2 + z] / nvar;
+    const double Bb = c.A * bs[K1 + (K2 - y) % K2] * bs[K1 + K2 + (K3 - z) % K3] / nvar;
     for (int v = 0; v < nvar; ++v) {
       double ms[3];
       int bit = 0;
@@ -880,8 +903,9 @@ __device__ __forceinline__ cplx<T> infl_general(const Args& a, const InflCol& c,
       double r = __builtin_amdgcn_rcp(msq);
       r = fma(r, fma(-msq, r, 1.0), r);
       r = fma(r, fma(-msq, r, 1.0), r);
-      const double Gv = Bw * exp(-c.fac * msq) * r;
-      const double e = c.wx * Gv * f2;
+      const double ex = exp(-c.fac * msq);
+      const double Ga = Ba * ex * r, Gb = Bb * ex * r;
+      const double e = fma(c.wx * Ga, f2a, c.wx * Gb * f2b);
       const double eu = e * (r + c.fac);
       acc[0] += e;
       acc[1] = fma(eu * mv[0], mv[0], acc[1]);
@@ -890,11 +914,65 @@ __device__ __forceinline__ cplx<T> infl_general(const Args& a, const InflCol& c,
       acc[4] = fma(eu * mv[0], mv[1], acc[4]);
       acc[5] = fma(eu * mv[0], mv[2], acc[5]);
       acc[6] = fma(eu * mv[1], mv[2], acc[6]);
-      gm += Gv;
+      ga += Ga;
+      gb += Gb;
     }
   }
-  const T g = (T)gm;
-  return {f.x * g, f.y * g};
+  const T g = (T)ga, h = (T)gb;
+  if (pair) fb = {vb.x * h, vb.y * h};
+  fa = {va.x * g, va.y * g};
+}
+template <class G, typename T>
+__device__ __forceinline__ cplx<T> infl_general(const Args& a, const InflCol& c, int xp, int y,
+                                                int z, const double* bs, cplx<T> f, double* acc) {
+  infl_general<G>(a, c, xp, y, z, bs, f, f, false, acc);
+  return f;
+}
+
+// The influence function on a whole column, element (y, z) at buf[z * PZ + y].
+// Orthorhombic: mirrored modes together (a 72 x 72 column 3.0 -> 1.4 us).
+// General cell: the exponential of each mode and sign is the cost; modes with
+// a Nyquist index, which need two to eight, come last and by themselves (dealt
+// in order they put one such mode into every wavefront), and in the columns
+// m1 = 0 and K1/2 the modes m and -m are taken together (a 48 x 48 column 4.3,
+// and 7.1 us at K1/2, -> 2.4 us).
+template <class P, class G, int PZ, int VT>
+__device__ __forceinline__ void influence_column(const Args& a, cplx<typename P::real>* buf, int xp,
+                                                 const double* bs, double* acc, int vt) {
+  constexpr int K1 = G::K1, K2 = G::K2, K3 = G::K3;
+  constexpr int H2 = K2 / 2, H3 = K3 / 2;
+  const InflCol c = infl_col<G>(a, xp, bs);
+  auto at = [&](int y, int z) -> cplx<typename P::real>& { return buf[z * PZ + y]; };
+  if (!a.triclinic) {
+    for (int i = vt; i < (H2 + 1) * (H3 + 1); i += VT)
+      infl_mirror<G, true>(a, c, xp, i % (H2 + 1), i / (H2 + 1), bs, at, acc);
+    return;
+  }
+  const bool self = xp == 0 || 2 * xp == K1;  // m and -m both in this column
+  // modes without a Nyquist index, rounded up to whole wavefronts (self: half
+  // the z range, and of z = 0 half the y range); then those with one
+  const int nmain = (K2 - 1) * (self ? H3 : K3 - 1), main = (nmain + 63) & ~63;
+  const int nnyq = self ? H3 + 1 + H2 : K3 + K2 - 1;
+  for (int i = vt; i < main + nnyq; i += VT) {
+    int y, z;
+    if (i < main) {
+      if (i >= nmain) continue;
+      z = i / (K2 - 1);
+      y = i - z * (K2 - 1);
+      y += y >= H2;
+      if (!self) z += z >= H3;
+      if (self && z == 0 && y > H2) continue;  // its partner's
+    } else {
+      const int n = i - main, nz = self ? H3 + 1 : K3;  // y = H2 at nz z's, then z = H3
+      y = n < nz ? H2 : n - nz;
+      z = n < nz ? n : H3;
+      if (!self && n >= nz) y += y >= H2;
+    }
+    const int yb = (K2 - y) % K2, zb = (K3 - z) % K3;
+    const bool pair = self && (yb != y || zb != z);
+    cplx<typename P::real>& f = at(y, z);
+    infl_general<G>(a, c, xp, y, z, bs, f, pair ? at(yb, zb) : f, pair, acc);
+  }
 }
 
 template <class P, class G, int CY, int PZ, int VT>
@@ -908,14 +986,12 @@ __device__ __forceinline__ void influence(const Args& a, cplx<typename P::real>*
       buf[z * PZ + yy] = infl_general<G>(a, c, xp, y0 + yy, z, bs, buf[z * PZ + yy], acc);
     }
   } else {
-    constexpr int NIT = (K3 * CY + VT - 1) / VT;
-    constexpr int UNR = NIT <= 4 ? NIT : 2;
-#pragma unroll UNR
-    for (int it = 0; it < NIT; ++it) {
-      const int i = vt + it * VT;
-      if ((K3 * CY) % VT != 0 && i >= K3 * CY) break;
+    // modes z and K3 - z together
+    for (int i = vt; i < (K3 / 2 + 1) * CY; i += VT) {
       const int z = i / CY, yy = i - z * CY;
-      buf[z * PZ + yy] = infl_ortho<G>(a, c, xp, y0 + yy, z, bs, buf[z * PZ + yy], acc);
+      infl_mirror<G, false>(
+          a, c, xp, y0 + yy, z, bs,
+          [&](int y, int zz) -> cplx<typename P::real>& { return buf[zz * PZ + y - y0]; }, acc);
     }
   }
 }
@@ -1063,7 +1139,10 @@ k_conv(Args a_in, BatchArgs bt) {
     TRACE(2, 2);
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
-      influence<P, G, CY, PZ, VT>(a, buf, xp, y0, bs, acc[v], tid + v * NT);
+      if constexpr (NC == 1)
+        influence_column<P, G, PZ, VT>(a, buf, xp, bs, acc[v], tid + v * NT);
+      else
+        influence<P, G, CY, PZ, VT>(a, buf, xp, y0, bs, acc[v], tid + v * NT);
       // (one virtual thread's sums written before the next one's start)
       if constexpr (EARLY_EV) ev_row(a, acc[v], xp * (VT / 64) + ((tid + v * NT) >> 6));
     }
@@ -1810,9 +1889,9 @@ hipError_t with_batch(const BatchArgs* bt, F&& f) {
 // half spectrum in LDS from the first contribution to the last force.  At this
 // size each of the step's four launches is a chain of latencies -- launch,
 // arguments, counts, records, stores -- around a few hundred nanoseconds of
-// work.  192 atoms, p = 4: 18.2 -> 13.5 us, of which loads and tables 1.4,
-// spreading 2.4 (LDS atomics), transforms 5.4, influence function 2.2 (FP64
-// rate of one CU), interpolation 1.5, energy 0.9.  The arithmetic is that of the separate kernels (the same splines,
+// work.  192 atoms, p = 4: 18.2 -> 12.6 us, of which loads and tables 1.4,
+// spreading 2.4 (LDS atomics), transforms 5.4, influence function 1.2,
+// interpolation 1.5, energy 0.9.  The arithmetic is that of the separate kernels (the same splines,
 // butterflies, influence function and, between the stages, the same rounding
 // to the stored spectrum format).  The records, the counts and the spectrum
 // are also left in the workspace, so that a gather or a debug copy may follow.
@@ -1936,12 +2015,20 @@ __global__ __launch_bounds__(kSmallThreads) void k_step_small(Args a) {
   // atoms, while the others add up their energy and virial)
   constexpr int VT0 = 256;
   double acc[7] = {0, 0, 0, 0, 0, 0, 0};
-  for (int i = tid - VT0; i >= 0 && i < KH * NROW; i += NT - VT0) {
-    const int row = i / KH, xp = i - row * KH, z = row / K2, y = row - z * K2;
-    const InflCol c = infl_col<G>(a, xp, bs);
-    cplx<T>& f = rows[row * PC + xp];
-    f = a.triclinic ? infl_general<G>(a, c, xp, y, z, bs, f, acc)
-                    : infl_ortho<G>(a, c, xp, y, z, bs, f, acc);
+  if (!a.triclinic) {
+    constexpr int H2 = K2 / 2 + 1, H3 = K3 / 2 + 1;
+    for (int i = tid - VT0; i >= 0 && i < KH * H2 * H3; i += NT - VT0) {
+      const int xp = i % KH, y = i / KH % H2, z = i / (KH * H2);
+      infl_mirror<G, true>(a, infl_col<G>(a, xp, bs), xp, y, z, bs,
+                           [&](int yy, int zz) -> cplx<T>& { return rows[(zz * K2 + yy) * PC + xp]; },
+                           acc);
+    }
+  } else {
+    for (int i = tid - VT0; i >= 0 && i < KH * NROW; i += NT - VT0) {
+      const int row = i / KH, xp = i - row * KH, z = row / K2, y = row - z * K2;
+      cplx<T>& f = rows[row * PC + xp];
+      f = infl_general<G>(a, infl_col<G>(a, xp, bs), xp, y, z, bs, f, acc);
+    }
   }
   __syncthreads();
   TRACE(2, 5);
