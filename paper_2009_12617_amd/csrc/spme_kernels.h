@@ -883,7 +883,9 @@ __device__ __forceinline__ void infl_general(const Args& a, const InflCol& c, in
   double ga = 0.0, gb = 0.0;  // G(m), averaged over the Nyquist signs
   if (xp != 0 || y != 0 || z != 0) {
     const double Ba = c.A * bs[K1 + y] * bs[K1 + K2 + z] / nvar;
-    const double Bb = c.A * bs[K1 + (K2 - y) % K2] * bs[K1 + K2 + (K3 - z) % K3] / nvar;
+    // (only of a pair: the factors of -m need not be there otherwise)
+    const double Bb =
+        pair ? c.A * bs[K1 + (K2 - y) % K2] * bs[K1 + K2 + (K3 - z) % K3] / nvar : 0.0;
     for (int v = 0; v < nvar; ++v) {
       double ms[3];
       int bit = 0;

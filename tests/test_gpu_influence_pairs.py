@@ -4,7 +4,7 @@ the virial and the convolved spectrum, against the plain formula on every mode
 in FP64 -- each index averaged over its two signs at the Nyquist point.  Grids
 whose halves do and do not fill whole wavefronts, both kinds of cell; FP64
 plans, where nothing but rounding (some hundred FP64 operations per mode)
-separates the two: 1e-12."""
+separates the two: 1e-12.  The other convolutions in FP32, 2e-6."""
 import itertools
 
 import numpy as np
@@ -58,26 +58,32 @@ def reference(grid, box, beta, p):
 
 
 @pytest.mark.parametrize("general", [False, True], ids=["orthorhombic", "general"])
-@pytest.mark.parametrize("K", [16, 24, 36, 48, 72, (48, 32, 64), 96], ids=str)
-def test_energy_virial_and_potential(P, K, general):
+@pytest.mark.parametrize("K,conv", [(16, 0), (24, 0), (36, 0), (48, 0), (72, 0), ((48, 32, 64), 0),
+                                    (96, 0), ((32, 32, 64), 1), (96, 1), (32, 2), (64, 2)], ids=str)
+def test_energy_virial_and_potential(P, K, conv, general):
     shape = (K,) * 3 if np.ndim(K) == 0 else K
-    pos, q, _ = I.water_box(60, 0.8 * shape[0], 11)
+    # (the split convolution holds part of the factors in LDS: enough atoms
+    # that the spreading before it leaves negative integers, NaN as FP64, there)
+    prec = "fp64" if conv == 0 else "fp32_fixed"
+    pos, q, _ = I.water_box(60 if conv == 0 else 6000, 0.8 * shape[0], 11)
     edges = 0.8 * np.asarray(shape, dtype=np.float64)
     box = np.diag(edges)
     if general:
         box[1, 0], box[2, 0], box[2, 1] = 0.13 * edges[0], -0.08 * edges[0], 0.11 * edges[1]
     pos = pos / (0.8 * shape[0]) @ box
-    plan = P.Plan(shape, 4, 0.34, max_atoms=len(q), precision="fp64")
+    plan = P.Plan(shape, 4, 0.34, max_atoms=len(q), precision=prec)
     dp, dq = (torch.from_numpy(np.ascontiguousarray(a, dtype=np.float64)).to("cuda") for a in (pos, q))
     plan.set_debug(True)
-    plan.set_tuning(conv=0)
+    plan.set_tuning(conv=conv)
     _, ev = plan.step(dp, dq, box)
-    want, phi = reference(plan.debug_grid(0).cpu().numpy(), box, 0.34, 4)
+    grid = plan.debug_grid(0).cpu().numpy().astype(np.float64)
+    want, phi = reference(grid if conv == 0 else grid / 2.0 ** plan.frac_bits, box, 0.34, 4)
+    bar = 1e-12 if conv == 0 else 2e-6  # FP32 transforms, as the other parity tests
     got = ev.cpu().numpy()
-    assert np.abs(got - want).max() <= 1e-12 * np.abs(want).max()
+    assert np.abs(got - want).max() <= bar * np.abs(want).max()
     have = plan.debug_grid(2).cpu().numpy()
-    assert np.abs(have - phi).max() <= 1e-12 * np.abs(phi).max()
+    assert np.abs(have - phi).max() <= bar * np.abs(phi).max()
     # the one-launch and the separate steps agree
     plan.set_debug(False)
     _, again = plan.step(dp, dq, box)
-    assert np.abs(again.cpu().numpy() - want).max() <= 1e-12 * np.abs(want).max()
+    assert np.abs(again.cpu().numpy() - want).max() <= bar * np.abs(want).max()
