@@ -49,6 +49,7 @@ struct pme_plan {
   int grid_kept = 0;
   // kernel variants (pme_tuning)
   int conv_mode = 0, interp_mode = 0, bin_chunk = 1024;
+  int chunk_set = 0;  // bin_chunk was set (not the built-in default)
   // per-kernel timing
   int timing = 0;
   std::vector<hipEvent_t> event_pool;
@@ -291,7 +292,7 @@ bool box_recip(const double* box, double* rec, double* vol) {
 
 // Validate one step's inputs and fill the per-step fields of a.
 int set_inputs(pme_plan* p, Args& a, const double* pos, const double* q, int N,
-               const double box[9]) {
+               const double box[9], bool batched = false) {
   if (p == nullptr || box == nullptr || N < 0 || N > p->max_atoms) return PME_EINVAL;
   if (N > 0 && (pos == nullptr || q == nullptr)) return PME_EINVAL;
   for (int i = 0; i < 9; ++i)
@@ -302,7 +303,6 @@ int set_inputs(pme_plan* p, Args& a, const double* pos, const double* q, int N,
   double rec[9], vol = 0.0;
   if (!diag && !box_recip(box, rec, &vol)) return PME_EINVAL;
   a.N = N;
-  a.n_chunks = (N + p->bin_chunk - 1) / p->bin_chunk;
   a.pos = pos;
   a.q = q;
   a.triclinic = diag ? 0 : 1;
@@ -323,6 +323,9 @@ int set_inputs(pme_plan* p, Args& a, const double* pos, const double* q, int N,
   }
   a.keep_grid = p->keep_grid;
   apply_tuning(p, a);
+  // (batched binning launches share one chunk size)
+  if (!p->chunk_set && !batched) a.bin_chunk = spme::default_bin_chunk(N);
+  a.n_chunks = (N + a.bin_chunk - 1) / a.bin_chunk;
   a.forces = nullptr;
   a.ev = nullptr;
   a.reduce_ev = 0;
@@ -479,7 +482,7 @@ int pme_bind(pme_plan* p, const double* pos, const double* q, int N, const doubl
   if (p == nullptr) return PME_EINVAL;
   if (N > 0 && forces == nullptr) return PME_EINVAL;
   Args b = p->cur;  // plan constants (grid, order, precision, tables, layout)
-  int rc = set_inputs(p, b, pos, q, N, box);
+  int rc = set_inputs(p, b, pos, q, N, box, true);
   if (rc != PME_OK) return rc;
   b.forces = forces;
   b.accumulate = accumulate ? 1 : 0;
@@ -783,6 +786,7 @@ int pme_set_tuning(pme_plan* p, const pme_tuning* t) {
   p->conv_mode = t->conv;
   p->interp_mode = t->interp;
   p->bin_chunk = t->bin_chunk;
+  p->chunk_set = 1;
   apply_tuning(p, p->cur);
   return PME_OK;
 }

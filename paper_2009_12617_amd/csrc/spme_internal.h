@@ -176,6 +176,18 @@ hipError_t launch_inv_x(const Args& a, hipStream_t s, const Timing& t = Timing()
 //     general cell: p = 4: 320 19.4 / 19.5, 448 20.3 / 19.8; FP64 p = 4: 128
 //     19.3 / 19.6, 192 20.3 / 20.0
 // -- so the line is drawn on N p^2.  (24^3 lost at every size: 25 / 19.)
+// Atoms per binning workgroup of a step on its own, where none was set.  Few
+// atoms: small workgroups spread over the CUs and start sooner.  Many: every
+// workgroup adds to most buckets' counters, so fewer of them.  Step at 256 /
+// 512 / 1024, us: 32^3 4,095 atoms 18.38 / 18.72 / 19.46 (FP64 19.40 / 20.05 /
+// 21.47), 48^3 5,000 26.71 / 26.58 / 27.31, 14,000 24.71 / 24.19 / 24.92, 64^3
+// 24,000 24.94 / 23.88 / 24.38, 32,000 26.17 / 24.66 / 24.90, 48,000 28.55 /
+// 26.03 / 25.93, 72^3 38,000 35.39 / 33.58 / 33.16, 128^3 209,715 93.8 / 80.0 /
+// 72.7.  (Two or four atoms per thread, for fewer workgroups still, gained
+// nothing: 128^3 72.6 and 74.1.)
+constexpr int default_bin_chunk(int N) {
+  return N <= 4608 ? 256 : N <= 28672 ? 512 : kBinThreads;
+}
 bool step_small_wins(const Args& a);
 hipError_t launch_step_small(const Args& a, hipStream_t s);
 hipError_t launch_interp(const Args& a, hipStream_t s, const Timing& t = Timing(),
