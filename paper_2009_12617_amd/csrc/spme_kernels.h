@@ -882,10 +882,12 @@ __device__ __forceinline__ void infl_general(const Args& a, const InflCol& c, in
   const double f2b = pair ? fma((double)vb.x, (double)vb.x, (double)vb.y * (double)vb.y) : 0.0;
   double ga = 0.0, gb = 0.0;  // G(m), averaged over the Nyquist signs
   if (xp != 0 || y != 0 || z != 0) {
-    const double Ba = c.A * bs[K1 + y] * bs[K1 + K2 + z] / nvar;
+    // 1/nvar, a power of two
+    const double share = nvar == 1 ? 1.0 : nvar == 2 ? 0.5 : nvar == 4 ? 0.25 : 0.125;
+    const double Ba = c.A * bs[K1 + y] * bs[K1 + K2 + z] * share;
     // (only of a pair: the factors of -m need not be there otherwise)
     const double Bb =
-        pair ? c.A * bs[K1 + (K2 - y) % K2] * bs[K1 + K2 + (K3 - z) % K3] / nvar : 0.0;
+        pair ? c.A * bs[K1 + (K2 - y) % K2] * bs[K1 + K2 + (K3 - z) % K3] * share : 0.0;
     for (int v = 0; v < nvar; ++v) {
       double ms[3];
       int bit = 0;
@@ -948,6 +950,15 @@ __device__ __forceinline__ void influence_column(const Args& a, cplx<typename P:
   if (!a.triclinic) {
     for (int i = vt; i < (H2 + 1) * (H3 + 1); i += VT)
       infl_mirror<G, true>(a, c, xp, i % (H2 + 1), i / (H2 + 1), bs, at, acc);
+    return;
+  }
+  if constexpr (K2 * K3 <= 256) {
+    // at most a wavefront per SIMD: nothing waits for its neighbours (16^3
+    // column 6.4 us like this, 6.9 as below)
+    for (int i = vt; i < K2 * K3; i += VT) {
+      cplx<typename P::real>& f = at(i % K2, i / K2);
+      f = infl_general<G>(a, c, xp, i % K2, i / K2, bs, f, acc);
+    }
     return;
   }
   const bool self = xp == 0 || 2 * xp == K1;  // m and -m both in this column
