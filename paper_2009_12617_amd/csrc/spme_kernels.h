@@ -547,8 +547,9 @@ __global__ __launch_bounds__(spread_threads<BATCH>()) void k_spread_x(Args a_in,
   // items: the records of the buckets one after another; kItems per thread
   // per pass so that their loads overlap.  (The bucket ends in scalar
   // registers: at p = 6 the kernel keeps to 64 vector registers, two
-  // workgroups to a CU; 128^3 p = 6 spreading 34.9 -> 30.6 us.)
-  constexpr int kItems = 4;
+  // workgroups to a CU; 128^3 p = 6 spreading 34.9 -> 30.6 us.)  At p = 4 a
+  // tile holds one to two records per thread, and two are enough.
+  constexpr int kItems = ORDER > 4 ? 4 : 2;
   int end[NBK];
 #pragma unroll
   for (int k = 0; k < NBK; ++k) end[k] = __builtin_amdgcn_readfirstlane(bk_end[k]);
