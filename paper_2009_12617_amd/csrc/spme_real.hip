@@ -53,7 +53,7 @@ constexpr int kRsSortTable = 2048, kRsSmall = 8 * kRsSortThreads;  // sub-cells 
 // that consecutive atoms of a row of cells lie close together (the box of a
 // workgroup's home atoms, which bounds their candidates, is then small).
 constexpr int kRsSlabs = 8;
-constexpr float kRsFar = 1e30f;
+constexpr float kRsFar = 1e30f;  // (of lengths in units of the box: RsArgs::unit_len)
 
 struct RsArgs {
   int N, nc[3], ncell, n_count_blocks;
@@ -66,7 +66,12 @@ struct RsArgs {
   int split;             // wavefronts of a pair workgroup
   int unit, nunit, nblk;  // cells of a home unit, units, pair workgroups per unit
   int max_span;          // most cells a group may reach past its first one
-  double ext2;           // (half the box diagonal + rcut)^2
+  // The FP32 tests take lengths times unit_len, the power of two that brings
+  // half the box diagonal + rcut into [1, 2): their squares neither overflow
+  // nor vanish whatever the unit of length, and no rounding is added.
+  double unit_len, len_unit;  // ... and its inverse
+  float list_lim;        // listing: rcut^2 and the margin of the whole box
+  double slack;          // most that FP32 moves a coordinate relative to the box centre
   const double* pos;
   const double* q;
   const int* excl_off;  // may be null
@@ -79,7 +84,7 @@ struct RsArgs {
   unsigned* start;      // [ncell * kRsSlabs + 1]
   unsigned* rank;       // [N] place of each atom within its sub-cell
   double4* rec;         // [N] wrapped position and charge, in cell order
-  float4* rec32;        // [N] position relative to the box centre in FP32 and its square
+  float4* rec32;        // [N] position relative to the box centre (times unit_len) in FP32 and its square
   int* ridx;            // [N] original index, in cell order
   double* rows;         // [nrow] pair energies; [n_count_blocks] q^2 sums; [n_count_blocks] exclusions
 };
@@ -169,8 +174,8 @@ __device__ __forceinline__ void table_scan(unsigned* table, unsigned* wsum) {
 // One atom into its place in cell order.
 __device__ __forceinline__ void place(const RsArgs& a, int i, unsigned slot, const double* w, double qi) {
   a.rec[slot] = make_double4(w[0], w[1], w[2], qi);
-  const float x = (float)(w[0] - 0.5 * a.L[0]), y = (float)(w[1] - 0.5 * a.L[1]),
-              z = (float)(w[2] - 0.5 * a.L[2]);
+  const float x = (float)((w[0] - 0.5 * a.L[0]) * a.unit_len), y = (float)((w[1] - 0.5 * a.L[1]) * a.unit_len),
+              z = (float)((w[2] - 0.5 * a.L[2]) * a.unit_len);
   const float sq = x * x + y * y + z * z;
   // (a non-finite position is never within the cutoff of anything)
   a.rec32[slot] = sq < kRsFar ? make_float4(x, y, z, sq) : make_float4(0.f, 0.f, 0.f, kRsFar);
@@ -388,8 +393,9 @@ __device__ __forceinline__ void rs_pair(const RsArgs& a, const RsConst& k, const
   double r2 = d[0] * d[0] + d[1] * d[1] + d[2] * d[2];
   // (the home atom's own record, and an atom on the same position, lie at
   // distance exactly 0 and add nothing)
-  const double qq = ok && r2 <= a.rc2 && r2 > 0.0 ? ri.w * rj.w : 0.0;
-  r2 = fmax(r2, 1e-100);
+  const bool in = ok && r2 <= a.rc2 && r2 > 0.0;
+  const double qq = in ? ri.w * rj.w : 0.0;
+  r2 = in ? r2 : a.rc2;  // (keeps every factor of qq = 0 finite)
   double rinv = __builtin_amdgcn_rsq(r2);
   const double u = fma(-(r2 * rinv), rinv, 1.0);
   rinv = fma(fma(u, 0.375, 0.5), u * rinv, rinv);
@@ -428,10 +434,11 @@ using f32x4 = __attribute__((__vector_size__(4 * sizeof(float)))) float;
 // matrix instruction,
 //   |j|^2 - 2 i.j + (|i|^2 - rcut^2 - margin),
 // relative to the centre of the home atoms' box.  A negative value may be a
-// pair, which the pair evaluation decides in FP64.  Every candidate lies
-// within ext of the centre and every home atom closer, so rounding moves the
-// sum by less than 44 2^-24 ext^2 = 2.7e-6 ext^2; the margin is 4e-6 ext^2,
-// so no pair is missed.  Lane (g, col) receives rows 4g .. 4g+3 of a tile and
+// pair, which the pair evaluation decides in FP64.  Every candidate that may
+// be one lies within ext of the centre (ext: half the box's diagonal + rcut,
+// and slack for the rounding of the box itself) and every home atom closer, so
+// rounding moves the sum by less than 44 2^-24 ext^2 = 2.7e-6 ext^2; the margin
+// is 4e-6 ext^2, so no pair is missed.  Lane (g, col) receives rows 4g .. 4g+3 of a tile and
 // shifts their sign bits into a mask word; a word covers 8 tiles.
 //
 // Pair evaluation: each lane walks its own hits, the next candidate being
@@ -468,6 +475,7 @@ __global__ __launch_bounds__(kRsThreads, S == 1 ? 3 : 2) void k_rs_pairs(RsArgs 
   __shared__ unsigned list[kRsList];    // record | segment << kRsIdxBits
   __shared__ unsigned masks_all[kRsWaves][kWords + 2][64];  // two words of zeros at the end
   __shared__ double seg_shift[kRsSegs][3];
+  __shared__ float seg_unit[kRsSegs][3];  // the same times unit_len
   __shared__ int seg_start[kRsSegs], seg_pre[32];  // (seg_pre: the segments' first items, then INT_MAX)
   __shared__ double two_to[kRsExp];
   __shared__ double home_f[S > 1 ? kRsHome / S : 1][3];
@@ -543,6 +551,9 @@ __global__ __launch_bounds__(kRsThreads, S == 1 ? 3 : 2) void k_rs_pairs(RsArgs 
         seg_shift[lane][0] = im * a.L[0];
         seg_shift[lane][1] = sy;
         seg_shift[lane][2] = sz;
+        seg_unit[lane][0] = (float)(im * a.L[0] * a.unit_len);
+        seg_unit[lane][1] = (float)(sy * a.unit_len);
+        seg_unit[lane][2] = (float)(sz * a.unit_len);
       }
       int inc = n;
 #pragma unroll
@@ -582,16 +593,19 @@ __global__ __launch_bounds__(kRsThreads, S == 1 ? 3 : 2) void k_rs_pairs(RsArgs 
     const bool active = col < nh && a.rec32[own].w < kRsFar;
     __syncthreads();
     const int total = nitem;
-    auto centre = [&](int d) { return 0.5 * a.L[d] + 0.5 * (hbox[d] + hbox[3 + d]); };
-    // the matrix instruction's column (-2 i, 1) and |i|^2 - rcut^2 - margin
+    auto centre = [&](int d) { return 0.5 * a.L[d] + 0.5 * (hbox[d] + hbox[3 + d]) * a.len_unit; };
+    // the matrix instruction's column (-2 i, 1) and |i|^2 - rcut^2 - margin,
+    // lengths times unit_len
     float bcol, q;
     {
-      const float x = (float)(ri.x - centre(0)), y = (float)(ri.y - centre(1)), z = (float)(ri.z - centre(2));
+      const float x = (float)((ri.x - centre(0)) * a.unit_len), y = (float)((ri.y - centre(1)) * a.unit_len),
+                  z = (float)((ri.z - centre(2)) * a.unit_len);
       const float v = g4 == 0 ? x : g4 == 1 ? y : z;
       const double w[3] = {(double)hbox[3] - hbox[0], (double)hbox[4] - hbox[1], (double)hbox[5] - hbox[2]};
-      const double ext = 0.5 * sqrt(w[0] * w[0] + w[1] * w[1] + w[2] * w[2]) + a.rcut;
+      const double rc = a.rcut * a.unit_len;
+      const double ext = 0.5 * sqrt(w[0] * w[0] + w[1] * w[1] + w[2] * w[2]) + rc + a.slack;
       bcol = g4 == 3 ? 1.f : active ? -2.f * v : 0.f;
-      q = active ? (float)((double)x * x + (double)y * y + (double)z * z - a.rc2 - 4e-6 * ext * ext) : kRsFar;
+      q = active ? (float)((double)x * x + (double)y * y + (double)z * z - rc * rc - 4e-6 * ext * ext) : kRsFar;
     }
     double f[3] = {0.0, 0.0, 0.0};
     for (int s0 = 0; s0 < total;) {
@@ -602,7 +616,7 @@ __global__ __launch_bounds__(kRsThreads, S == 1 ? 3 : 2) void k_rs_pairs(RsArgs 
       if (tid == 0) listed = 0;
       __syncthreads();
       int cnt = 0;
-      const float lim = (float)(a.rc2 + 4e-6 * a.ext2);
+      const float lim = a.list_lim;
       do {
         const int n = min(total - s0, kRsList - cnt);
         float4 ahead[kRsPer];
@@ -631,9 +645,8 @@ __global__ __launch_bounds__(kRsThreads, S == 1 ? 3 : 2) void k_rs_pairs(RsArgs 
           int nkept = 0;
 #pragma unroll
           for (int j = 0; j < kRsPer; ++j) {
-            const double* sh = seg_shift[item[j] >> kRsIdxBits];
-            const float x = cand[j].x + (float)sh[0], y = cand[j].y + (float)sh[1],
-                        z = cand[j].z + (float)sh[2];
+            const float* sh = seg_unit[item[j] >> kRsIdxBits];
+            const float x = cand[j].x + sh[0], y = cand[j].y + sh[1], z = cand[j].z + sh[2];
             const float dx = fmaxf(fmaxf(hbox[0] - x, x - hbox[3]), 0.f);
             const float dy = fmaxf(fmaxf(hbox[1] - y, y - hbox[4]), 0.f);
             const float dz = fmaxf(fmaxf(hbox[2] - z, z - hbox[5]), 0.f);
@@ -680,7 +693,8 @@ __global__ __launch_bounds__(kRsThreads, S == 1 ? 3 : 2) void k_rs_pairs(RsArgs 
             y = r.y + sh[1];
             z = r.z + sh[2];
             qj = r.w;
-            const float fx = (float)(x - ctr[0]), fy = (float)(y - ctr[1]), fz = (float)(z - ctr[2]);
+            const float fx = (float)((x - ctr[0]) * a.unit_len), fy = (float)((y - ctr[1]) * a.unit_len),
+                        fz = (float)((z - ctr[2]) * a.unit_len);
             sq = fx * fx + fy * fy + fz * fz;
           }
           stage[0][slot] = x;
@@ -692,7 +706,8 @@ __global__ __launch_bounds__(kRsThreads, S == 1 ? 3 : 2) void k_rs_pairs(RsArgs 
         __syncthreads();
         if (nh <= 0) continue;
         // --- distance tests
-        const double cg = g4 == 3 ? 0.0 : (g4 == 0 ? ctr[0] : g4 == 1 ? ctr[1] : ctr[2]);
+        const double sc = g4 == 3 ? 1.0 : a.unit_len;
+        const double cg = g4 == 3 ? 0.0 : (g4 == 0 ? ctr[0] : g4 == 1 ? ctr[1] : ctr[2]) * sc;
         const int slot0 = spl * 4 * pitch;
         {
           // this lane's component of row col: tile b of word w lies 32 w + 4 b slots on
@@ -700,7 +715,7 @@ __global__ __launch_bounds__(kRsThreads, S == 1 ? 3 : 2) void k_rs_pairs(RsArgs 
           for (int w = 0; w < nw; ++w, src += 32) {
             float v[8];
 #pragma unroll
-            for (int b = 0; b < 8; ++b) v[b] = (float)(src[4 * b] - cg);
+            for (int b = 0; b < 8; ++b) v[b] = (float)fma(src[4 * b], sc, -cg);
             f32x4 dd[8];
 #pragma unroll
             for (int b = 0; b < 8; ++b)
@@ -955,7 +970,13 @@ int pme_real(const double* pos, const double* q, int N, const double box[9], dou
   a.nunit = a.ncell / a.unit;
   a.max_span = a.unit > 1 ? std::min(a.nc[0] - 3, 2) : 0;
   const double ext = 0.5 * std::sqrt(L[0] * L[0] + L[1] * L[1] + L[2] * L[2]) + rcut;
-  a.ext2 = ext * ext;
+  int e2 = 0;
+  (void)std::frexp(ext, &e2);
+  a.unit_len = std::ldexp(1.0, 1 - e2);
+  a.len_unit = std::ldexp(1.0, e2 - 1);
+  const double eu = ext * a.unit_len, ru = rcut * a.unit_len;
+  a.list_lim = (float)(ru * ru + 4e-6 * eu * eu);
+  a.slack = 0x1p-22 * eu;
   a.split = rs_split(N);
   a.nblk = rs_nblk(N, a.nunit, a.split);
   a.nrow = a.nunit * a.nblk;
