@@ -950,7 +950,8 @@ int pme_real(const double* pos, const double* q, int N, const double box[9], dou
   RsArgs a{};
   long long ncell = 1;
   for (int d = 0; d < 3; ++d) {
-    a.nc[d] = (int)std::floor(L[d] / rcut);
+    // (no axis ends with more than max_cells; the product of three fits)
+    a.nc[d] = (int)std::min(std::floor(L[d] / rcut), (double)max_cells);
     if (a.nc[d] < 3) return PME_EUNSUPPORTED;  // rcut must be <= L/3 along every axis
     ncell *= a.nc[d];
   }

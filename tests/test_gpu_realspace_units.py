@@ -2,6 +2,8 @@
 times 2^k and beta over 2^k is the same system, with energies over 2^k and
 forces over 2^2k (powers of two, so that only the order of additions may
 differ), and a box may be any number of times larger than the cutoff."""
+import math
+
 import numpy as np
 import pytest
 import torch
@@ -51,3 +53,28 @@ def test_cluster_in_a_large_box(P, edge):
     err = np.linalg.norm(f.cpu().numpy() - ref["forces"])
     assert err <= 1e-11 * np.linalg.norm(ref["forces"])
     assert float(e[0]) == pytest.approx(ref["E_real"], rel=1e-12)
+
+
+@pytest.mark.parametrize("rcut", [1e-4, 1e-6, 1e-9, 1e-12])
+def test_cutoff_far_below_the_box(P, rcut):
+    # L / rcut past 2^21 (the product of three such counts is past 64 bits)
+    # and past 2^31: the grid has max_cells at most
+    rng = np.random.default_rng(6)
+    n, beta = 300, 3.0 / rcut
+    pos, q = rng.random((n, 3)) * 100.0, rng.uniform(-1.0, 1.0, size=n)
+    pos[:40] = rcut * rng.random((40, 3)) * 2.0  # near the origin, where such distances exist
+    real = P.RealSpace(n, max_cells=1000)
+    f, e = real(dev(pos), dev(q), np.diag([100.0] * 3), beta, rcut)
+    f, want, E = f.cpu().numpy(), np.zeros((n, 3)), 0.0
+    for i in range(40):
+        for j in range(40):
+            d = pos[i] - pos[j]
+            r = math.sqrt(float(d @ d / rcut / rcut)) * rcut
+            if i != j and r <= rcut:
+                u = q[i] * q[j] * math.erfc(beta * r) / r
+                g = q[i] * q[j] * 2 * beta / math.sqrt(math.pi) * math.exp(-(beta * r) ** 2)
+                E += 0.5 * u
+                want[i] += (u + g) / r * (d / r)
+    f, want = f * rcut * rcut, want * rcut * rcut
+    assert np.linalg.norm(f - want) <= 1e-11 * np.linalg.norm(want)
+    assert float(e[0]) == pytest.approx(E, rel=1e-11)
