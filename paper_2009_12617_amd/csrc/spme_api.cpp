@@ -48,8 +48,7 @@ struct pme_plan {
   int keep_grid = 0;
   int grid_kept = 0;
   // kernel variants (pme_tuning)
-  int conv_mode = 0, interp_mode = 0, bin_chunk = 1024;
-  int chunk_set = 0;  // bin_chunk was set (not the built-in default)
+  int conv_mode = 0, interp_mode = 0, bin_chunk = spme::kBinThreads;
   // per-kernel timing
   int timing = 0;
   std::vector<hipEvent_t> event_pool;
@@ -323,8 +322,9 @@ int set_inputs(pme_plan* p, Args& a, const double* pos, const double* q, int N,
   }
   a.keep_grid = p->keep_grid;
   apply_tuning(p, a);
-  // (batched binning launches share one chunk size)
-  if (!p->chunk_set && !batched) a.bin_chunk = spme::default_bin_chunk(N);
+  // the built-in chunk goes by the number of atoms (batched binning launches
+  // share one size); a smaller one was chosen
+  if (p->bin_chunk == spme::kBinThreads && !batched) a.bin_chunk = spme::default_bin_chunk(N);
   a.n_chunks = (N + a.bin_chunk - 1) / a.bin_chunk;
   a.forces = nullptr;
   a.ev = nullptr;
@@ -760,7 +760,7 @@ int pme_default_tuning(int K1, int K2, int K3, int order, int precision, pme_tun
   if (out == nullptr) return PME_EINVAL;
   if (spme::variants_for(K1, K2, K3, order, precision) == 0u) return PME_EUNSUPPORTED;
   spme::default_variants(K1, K2, K3, order, precision, &out->conv, &out->interp);
-  out->bin_chunk = 1024;
+  out->bin_chunk = spme::kBinThreads;
   return PME_OK;
 }
 
@@ -786,7 +786,6 @@ int pme_set_tuning(pme_plan* p, const pme_tuning* t) {
   p->conv_mode = t->conv;
   p->interp_mode = t->interp;
   p->bin_chunk = t->bin_chunk;
-  p->chunk_set = 1;
   apply_tuning(p, p->cur);
   return PME_OK;
 }

@@ -176,7 +176,7 @@ hipError_t launch_inv_x(const Args& a, hipStream_t s, const Timing& t = Timing()
 //     general cell: p = 4: 320 19.4 / 19.5, 448 20.3 / 19.8; FP64 p = 4: 128
 //     19.3 / 19.6, 192 20.3 / 20.0
 // -- so the line is drawn on N p^2.  (24^3 lost at every size: 25 / 19.)
-// Atoms per binning workgroup of a step on its own, where none was set.  Few
+// Atoms per binning workgroup of a step on its own, of the built-in choice.  Few
 // atoms: small workgroups spread over the CUs and start sooner.  Many: every
 // workgroup adds to most buckets' counters, so fewer of them.  Step at 256 /
 // 512 / 1024, us: 32^3 4,095 atoms 18.38 / 18.72 / 19.46 (FP64 19.40 / 20.05 /
