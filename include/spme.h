@@ -230,7 +230,10 @@ typedef struct {
  * parameters are unsupported).  Host only. */
 unsigned pme_tuning_variants(int K1, int K2, int K3, int order, int precision);
 
-/* The built-in choice for these parameters (PME_EUNSUPPORTED when none). */
+/* The built-in choice for these parameters (PME_EUNSUPPORTED when none).
+ * With it, pme_step on a 16^3 grid takes a step of few atoms in one launch,
+ * which the variants do not enter; with any other choice it runs the
+ * variants chosen. */
 int pme_default_tuning(int K1, int K2, int K3, int order, int precision, pme_tuning *out);
 
 /* Read or change a plan's variants.  pme_set_tuning returns
@@ -241,7 +244,8 @@ int pme_default_tuning(int K1, int K2, int K3, int order, int precision, pme_tun
 int pme_get_tuning(pme_plan *plan, pme_tuning *out);
 int pme_set_tuning(pme_plan *plan, const pme_tuning *t);
 
-/* Autotuning: runs whole steps (pme_step with these arguments) of every
+/* Autotuning: runs whole steps (pme_step with these arguments, so the
+ * built-in choice's one-launch step where it takes one) of every
  * variant the plan supports -- each conv (fused, split, reg) x interp
  * (fused, split) x bin_chunk (256, 512, 1024) combination, in that nesting
  * order, bin_chunk fastest: 18 candidates -- `reps` timed steps each

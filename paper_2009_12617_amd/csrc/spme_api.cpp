@@ -49,6 +49,7 @@ struct pme_plan {
   int grid_kept = 0;
   // kernel variants (pme_tuning)
   int conv_mode = 0, interp_mode = 0, bin_chunk = spme::kBinThreads;
+  int conv_builtin = 0, interp_builtin = 0;  // the built-in choice of the plan's shape
   // per-kernel timing
   int timing = 0;
   std::vector<hipEvent_t> event_pool;
@@ -144,6 +145,8 @@ int init_plan(pme_plan* p, int K1, int K2, int K3, int order, double beta, int m
   p->stream = stream;
   p->lay = L;
   spme::default_variants(K1, K2, K3, order, precision, &p->conv_mode, &p->interp_mode);
+  p->conv_builtin = p->conv_mode;
+  p->interp_builtin = p->interp_mode;
   Args& a = p->cur;
   a.K1 = K1;
   a.K2 = K2;
@@ -378,12 +381,14 @@ int solve_impl(pme_plan* p, double* ev, bool fused) {
   return PME_OK;
 }
 
-// Whether a step may go in one launch: nothing between its stages is asked
-// for (the charge grid, kernel times), and no counts of an unfinished step
-// wait to be cleared.
+// Whether a step may go in one launch: no variant of the separate launches
+// was chosen, nothing between its stages is asked for (the charge grid, kernel
+// times), and no counts of an unfinished step wait to be cleared.
 bool one_launch_ok(const pme_plan* p, int N) {
-  return p->K1 * p->K2 * p->K3 <= spme::kSmallPoints && N >= 1 && !p->keep_grid && !p->timing &&
-         p->state != kSpread && p->state != kDirty;
+  const bool builtin = p->conv_mode == p->conv_builtin && p->interp_mode == p->interp_builtin &&
+                       p->bin_chunk == spme::kBinThreads;
+  return builtin && p->K1 * p->K2 * p->K3 <= spme::kSmallPoints && N >= 1 && !p->keep_grid &&
+         !p->timing && p->state != kSpread && p->state != kDirty;
 }
 
 // A whole step in one launch (inputs set).

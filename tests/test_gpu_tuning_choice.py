@@ -1,6 +1,7 @@
 """What a chosen tuning makes a step run, and what writing a tuning back leaves
-alone: the binning chunk of a lone step, read from the per-workgroup charge
-sums it leaves in the workspace."""
+alone: the binning chunk of a lone step (read from the per-workgroup charge
+sums it leaves in the workspace), the one-launch step of small systems, and
+the autotuner on them."""
 import numpy as np
 import pytest
 import torch
@@ -70,3 +71,44 @@ def test_smaller_chunks_run_as_set(P, n):
         assert chunk.ran(plan, n, edge) == m
     plan.set_tuning(bin_chunk=1024)
     assert chunk.ran(plan, n, edge) == chunk.ran(P.Plan(32, 4, 0.35, max_atoms=n), n, edge)
+
+
+def small(n=192):
+    rng = np.random.default_rng(n)
+    pos, box = system(n, 12.4, seed=n)
+    return pos, torch.from_numpy(rng.standard_normal(n)).to("cuda"), box
+
+
+@pytest.mark.parametrize("precision", ["fp32_fixed", "fp32_fixed_half"])
+@pytest.mark.parametrize("change", [{"interp": 1}, {"bin_chunk": 256}])
+def test_small_step_runs_the_variants_set(P, precision, change):
+    # the one launch adds its energy in an order of its own; under chosen
+    # variants a step has the bits of spread, solve and gather
+    pos, q, box = small()
+    plan = P.Plan(16, 4, 0.34, max_atoms=192, precision=precision)
+    default = plan.tuning
+    f1, ev1 = plan.step(pos, q, box)
+    plan.set_tuning(**change)
+    f, ev = plan.step(pos, q, box)
+    plan.spread(pos, q, box)
+    ev2 = plan.solve()
+    f2 = plan.gather()
+    assert torch.equal(ev, ev2) and torch.equal(f, f2)
+    assert not torch.equal(ev1, ev2) and torch.equal(f1, f2)
+    # the built-in choice back: the one launch again
+    plan.set_tuning(**default)
+    f, ev = plan.step(pos, q, box)
+    assert torch.equal(ev, ev1) and torch.equal(f, f1)
+
+
+def test_autotune_of_a_small_system_measures_both_forms(P):
+    # the chain takes 18 us to the one launch's 13
+    pos, q, box = small()
+    plan = P.Plan(16, 4, 0.34, max_atoms=192)
+    default = plan.tuning
+    r = plan.autotune(pos, q, box, reps=50)
+    times = {tuple(c.values()): us for c, us in r["candidates"] if us is not None}
+    mine = times.pop(tuple(default.values()))
+    print(f"built-in {mine:.2f} us, others {min(times.values()):.2f} us and more", flush=True)
+    assert min(times.values()) > 1.15 * mine
+    assert r["best"] == default and plan.tuning == default
