@@ -13,6 +13,8 @@
 //   k_rs_count   atoms per sub-cell, each atom's rank, self and exclusion terms
 //   k_rs_scan    prefix sum of the counts, where k_rs_fill does not do it
 //   k_rs_fill    atoms into (cell, slab) order
+//                (whichever of the three has the sums also lists the groups of
+//                home atoms of the pair workgroups)
 //   k_rs_pairs   the pair sum, forces to the caller's order
 //   k_rs_reduce  energies from the per-workgroup rows, in a fixed order
 // Arithmetic is FP64 throughout, but for tests that may only let too many
@@ -57,14 +59,14 @@ constexpr float kRsFar = 1e30f;  // (of lengths in units of the box: RsArgs::uni
 
 struct RsArgs {
   int N, nc[3], ncell, n_count_blocks;
-  int nrow;             // pair workgroups: nunit * nblk
+  int nrow;             // pair workgroups launched: at least as many as there are groups
   double L[3], invL[3], cell_inv[3];
   double beta, rc2, rcut, coulomb;
   double poly[kRsCheb];  // exp(x^2) erfc(x), x = beta r, as a polynomial in t = 2 r / rcut - 1
   int ncheb;             // terms the pair kernel uses: kRsChebShort or kRsCheb
   double two_over_rcut, exp_scale;  // 2 / rcut, -32 beta^2 / ln 2
   int split;             // wavefronts of a pair workgroup
-  int unit, nunit, nblk;  // cells of a home unit, units, pair workgroups per unit
+  int unit, nunit;       // cells of a home unit, units
   int max_span;          // most cells a group may reach past its first one
   // The FP32 tests take lengths times unit_len, the power of two that brings
   // half the box diagonal + rcut into [1, 2): their squares neither overflow
@@ -86,6 +88,8 @@ struct RsArgs {
   double4* rec;         // [N] wrapped position and charge, in cell order
   float4* rec32;        // [N] position relative to the box centre (times unit_len) in FP32 and its square
   int* ridx;            // [N] original index, in cell order
+  int4* groups;         // [nrow] first and last + 1 home atom, unit, of each pair workgroup
+  int* ngroup;          // groups, rounded up to a multiple of kXcds
   double* rows;         // [nrow] pair energies; [n_count_blocks] q^2 sums; [n_count_blocks] exclusions
 };
 
@@ -244,6 +248,59 @@ __device__ __forceinline__ void self_and_excluded(const RsArgs& a, int blk, doub
   }
 }
 
+// Workgroups are dispatched round-robin over the XCDs, each with its own L2.
+constexpr int kXcds = 8;
+
+// The home atoms of the pair workgroups, listed by a workgroup of NT threads:
+// each unit's atoms in groups of equal size, at most kRsHome / split.  From
+// the counts themselves, so that a box with dense and empty parts fills the
+// chip as a uniform one does (a fixed number of workgroups per unit, from the
+// mean density, took the groups of dense units one after the other: 65,535
+// atoms in a slab across a tenth of its box 646 us, now 180; a uniform box 146,
+// now 143).  XCD x takes
+// a contiguous eighth of the groups.  start(u): first atom of unit u.
+template <int NT, class Start>
+__device__ __forceinline__ void list_groups(const RsArgs& a, Start&& start, unsigned* wsum) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int most = kRsHome / a.split;
+  auto groups_of = [&](int u) { return u < a.nunit ? ((int)(start(u + 1) - start(u)) + most - 1) / most : 0; };
+  int mine = 0;
+  for (int u = tid; u < a.nunit; u += NT) mine += groups_of(u);
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) mine += __shfl_xor(mine, d);
+  if (lane == 0) wsum[wave] = (unsigned)mine;
+  __syncthreads();
+  int total = 0;
+  for (int w = 0; w < NT / 64; ++w) total += (int)wsum[w];
+  const int per = (total + kXcds - 1) / kXcds;
+  auto put = [&](int i, int4 g) { a.groups[i % per * kXcds + i / per] = g; };
+  int carry = 0;
+  for (int b = 0; b < a.nunit; b += NT) {
+    const int u = b + tid, n = groups_of(u);
+    int inc = n;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const int o = __shfl_up(inc, d);
+      if (lane >= d) inc += o;
+    }
+    __syncthreads();  // the previous sums are read
+    if (lane == 63) wsum[wave] = (unsigned)inc;
+    __syncthreads();
+    int i = carry + inc - n;
+    for (int w = 0; w < NT / 64; ++w) {
+      if (w < wave) i += (int)wsum[w];
+      carry += (int)wsum[w];
+    }
+    if (n > 0) {
+      const int u0 = (int)start(u), u1 = (int)start(u + 1), gs = (u1 - u0 + n - 1) / n;
+      for (int k = 0; k < n; ++k)
+        put(i + k, make_int4(u0 + k * gs, min(u0 + (k + 1) * gs, u1), u, 0));
+    }
+  }
+  for (int i = total + tid; i < per * kXcds; i += NT) put(i, make_int4(0, 0, 0, 0));
+  if (tid == 0) *a.ngroup = per * kXcds;
+}
+
 // Small systems (at most PER atoms per thread and kRsSortTable sub-cells): workgroup 0
 // counts, scans and places every atom through LDS; the others do the self and
 // exclusion terms.  One launch in place of four.
@@ -284,6 +341,7 @@ __global__ __launch_bounds__(kRsSortThreads) void k_rs_sort(RsArgs a) {
     const int i = k * kRsSortThreads + tid;
     if (i < a.N) place(a, i, table[cell[k]] + rank[k], w[k], qi[k]);
   }
+  list_groups<kRsSortThreads>(a, [&](int u) { return table[u * a.unit * kRsSlabs]; }, wsum);
 }
 
 __global__ __launch_bounds__(256) void k_rs_zero(RsArgs a) {
@@ -306,7 +364,8 @@ __global__ __launch_bounds__(kRsCountThreads) void k_rs_count(RsArgs a) {
   self_and_excluded(a, blockIdx.x, wred);
 }
 
-// Exclusive prefix sum of more than kRsTable counts by one workgroup.
+// Exclusive prefix sum of more than kRsTable counts by one workgroup, and the
+// groups of the pair kernel.
 __global__ __launch_bounds__(kRsScanThreads) void k_rs_scan(RsArgs a) {
   __shared__ unsigned table[kRsTable + 1];
   __shared__ unsigned wsum[kRsScanThreads / 64];
@@ -322,14 +381,17 @@ __global__ __launch_bounds__(kRsScanThreads) void k_rs_scan(RsArgs a) {
     __syncthreads();
   }
   if (tid == 0) a.start[nsub] = carry;
+  __syncthreads();  // (the starts this workgroup wrote)
+  list_groups<kRsScanThreads>(a, [&](int u) { return a.start[(size_t)u * a.unit * kRsSlabs]; }, wsum);
 }
 
 // Atoms into cell order.  SCAN: at most kRsTable sub-cells, whose counts each
 // workgroup scans itself (a few microseconds less than a launch of its own);
-// the first writes the starts for the pair kernel.
+// one more, the first, writes the starts and the groups for the pair kernel.
 template <bool SCAN>
 __global__ __launch_bounds__(kRsCountThreads) void k_rs_fill(RsArgs a) {
-  const int tid = threadIdx.x, i = blockIdx.x * kRsCountThreads + tid;
+  const int tid = threadIdx.x, blk = SCAN ? (int)blockIdx.x - 1 : (int)blockIdx.x;
+  const int i = blk < 0 ? a.N : blk * kRsCountThreads + tid;
   double w[3] = {0.0, 0.0, 0.0}, qi = 0.0;
   int c = 0;
   unsigned r = 0u;
@@ -347,8 +409,11 @@ __global__ __launch_bounds__(kRsCountThreads) void k_rs_fill(RsArgs a) {
     for (int k = tid; k < kRsTable; k += kRsCountThreads) table[k] = k < nsub ? a.count[k] : 0u;
     __syncthreads();
     table_scan<kRsCountThreads, kRsTable>(table, wsum);
-    if (blockIdx.x == 0)
+    if (blk < 0) {
       for (int k = tid; k <= nsub; k += kRsCountThreads) a.start[k] = table[k];
+      list_groups<kRsCountThreads>(a, [&](int u) { return table[u * a.unit * kRsSlabs]; }, wsum);
+      return;
+    }
     if (i < a.N) place(a, i, table[c] + r, w, qi);
   } else {
     if (i < a.N) place(a, i, a.start[c] + r, w, qi);
@@ -410,11 +475,6 @@ __device__ __forceinline__ void rs_pair(const RsArgs& a, const RsConst& k, const
 #pragma unroll
   for (int c = 0; c < 3; ++c) f[c] = fma(g, d[c], f[c]);
 }
-
-// Workgroups are dispatched round-robin over the XCDs, each with its own L2:
-// XCD x takes a contiguous eighth of the logical indices (n a multiple of 8).
-constexpr int kXcds = 8;
-__device__ __forceinline__ int xcd_local(int b, int n) { return (b % kXcds) * (n / kXcds) + b / kXcds; }
 
 using f32x4 = __attribute__((__vector_size__(4 * sizeof(float)))) float;
 
@@ -482,21 +542,18 @@ __global__ __launch_bounds__(kRsThreads, S == 1 ? 3 : 2) void k_rs_pairs(RsArgs 
   __shared__ double home_e[kRsWaves];
   __shared__ float hbox[6];  // home atoms' box, relative to the box centre: low x y z, high x y z
   __shared__ int listed, nitem;
-  const int id = xcd_local(blockIdx.x, gridDim.x);
-  if (id >= a.nrow) return;
+  const int id = blockIdx.x;
+  const int4 group = a.groups[id];  // (of a workgroup past the last group: not written)
+  if (id >= *a.ngroup || group.x >= group.y) {
+    if (threadIdx.x == 0) a.rows[id] = 0.0;
+    return;
+  }
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int spl = wave % S;
   unsigned(*masks)[64] = masks_all[wave];
-  const int unit = id / a.nblk, blk = id - unit * a.nblk;
-  const int cell0 = unit * a.unit;  // the unit's first cell
-  const int u0 = (int)a.start[cell0 * kRsSlabs], u1 = (int)a.start[(cell0 + a.unit) * kRsSlabs];
-  const int used = (u1 - u0 + kRsHome / S - 1) / (kRsHome / S);
-  if (blk >= used) {
-    if (tid == 0) a.rows[id] = 0.0;
-    return;
-  }
-  const int gs = (u1 - u0 + used - 1) / used;  // groups of equal size
+  const int cell0 = __builtin_amdgcn_readfirstlane(group.z) * a.unit;  // the unit's first cell
+  const int gend = __builtin_amdgcn_readfirstlane(group.y);
   const int cx0 = cell0 % a.nc[0], cy = (cell0 / a.nc[0]) % a.nc[1], cz = cell0 / (a.nc[0] * a.nc[1]);
   const int col = lane & 15, g4 = lane >> 4;
   if (tid >= 64 && tid < 64 + kRsExp) two_to[tid - 64] = exp2((tid - 64) * (1.0 / kRsExp));
@@ -504,11 +561,9 @@ __global__ __launch_bounds__(kRsThreads, S == 1 ? 3 : 2) void k_rs_pairs(RsArgs 
   __asm__ __volatile__("" : "+v"(kc.exp_scale), "+v"(kc.two_over_rcut), "+v"(kc.dbeta));
   double e_pair = 0.0;
 
-  // (grp counts groups; a group whose atoms span more cells than may share
-  // their neighbours is taken in several parts, `first` to `last`)
-  int grp = blk, first = u0 + grp * gs;
-  while (grp < used) {
-    const int gend = min(u0 + (grp + 1) * gs, u1);
+  // (a group whose atoms span more cells than may share their neighbours is
+  // taken in several parts, `first` to `last`)
+  for (int first = __builtin_amdgcn_readfirstlane(group.x); first < gend;) {
     // cells (within the unit) of the first atom and of the last one allowed
     int ca = 0, cb = 0;
     for (int i0 = 0; i0 < a.unit; i0 += 64) {
@@ -522,7 +577,7 @@ __global__ __launch_bounds__(kRsThreads, S == 1 ? 3 : 2) void k_rs_pairs(RsArgs 
     int last = gend;
     if (cb - ca > a.max_span) {
       cb = ca + a.max_span;
-      last = (int)a.start[(cell0 + cb + 1) * kRsSlabs];
+      last = __builtin_amdgcn_readfirstlane((int)a.start[(cell0 + cb + 1) * kRsSlabs]);
     }
     const int ng = last - first;
     __syncthreads();  // the previous part is done with the tables
@@ -792,10 +847,6 @@ __global__ __launch_bounds__(kRsThreads, S == 1 ? 3 : 2) void k_rs_pairs(RsArgs 
       for (int d = 0; d < 3; ++d) out[d] = add ? out[d] + f[d] : f[d];
     }
     first = last;
-    if (first == gend) {
-      grp += a.nblk;
-      first = u0 + grp * gs;
-    }
   }
   double v[1] = {0.5 * e_pair};
   wave_sums<1>(v);
@@ -824,7 +875,7 @@ __global__ __launch_bounds__(kRsCountThreads) void k_rs_reduce(RsArgs a) {
 
 template <int NC>
 void launch_pairs(const RsArgs& a, hipStream_t s) {
-  const dim3 grid((a.nrow + kXcds - 1) / kXcds * kXcds), block(kRsThreads);
+  const dim3 grid(a.nrow), block(kRsThreads);
   switch (a.split) {
     case 1: k_rs_pairs<NC, 1><<<grid, block, 0, s>>>(a); break;
     case 2: k_rs_pairs<NC, 2><<<grid, block, 0, s>>>(a); break;
@@ -841,17 +892,19 @@ size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 // 21,000, 153 / 188 / 239 at 65,535.
 int rs_split(int N) { return N <= 5120 ? 4 : N <= 16384 ? 2 : 1; }
 
-// Pair workgroups per home unit: enough for a unit 5% over the average, and
-// one more (an idle workgroup costs far less than one that takes two groups
-// one after the other).
-int rs_nblk(int N, int nunit, int split) {
-  return (int)std::ceil((double)N / nunit * (1.05 * split / kRsHome)) + 1;
+// Pair workgroups launched: no fewer than the groups that list_groups makes of
+// N atoms in nunit units (each unit's last may be part full, none is empty).
+int rs_rows(int N, int nunit, int split) {
+  const long long n = std::min<long long>(N, (long long)N * split / kRsHome + nunit);
+  return (int)((n + kXcds - 1) / kXcds * kXcds);
 }
-// Upper bound of nunit * rs_nblk(N, nunit).
-size_t rs_rows(int max_atoms, int max_cells) { return (size_t)max_atoms / 8 + 3 * (size_t)max_cells + 64; }
+// Upper bound of it.
+size_t rs_max_rows(int max_atoms, int max_cells) {
+  return (size_t)max_atoms * 4 / kRsHome + (size_t)max_cells + kXcds;
+}
 
 struct RsLayout {
-  size_t count, start, rank, rec, rec32, ridx, rows, total;
+  size_t count, start, rank, rec, rec32, ridx, groups, ngroup, rows, total;
 };
 
 RsLayout rs_layout(int max_atoms, int max_cells) {
@@ -866,7 +919,9 @@ RsLayout rs_layout(int max_atoms, int max_cells) {
   // (tiles of 16 read past the last record of a cell)
   L.rec32 = o;   o = align256(o + ((size_t)max_atoms + kRsGroup) * sizeof(float4));
   L.ridx = o;    o = align256(o + (size_t)max_atoms * sizeof(int));
-  L.rows = o;    o = align256(o + (rs_rows(max_atoms, max_cells) + 2 * (size_t)nblk) * sizeof(double));
+  L.groups = o;  o = align256(o + rs_max_rows(max_atoms, max_cells) * sizeof(int4));
+  L.ngroup = o;  o = align256(o + sizeof(int));
+  L.rows = o;    o = align256(o + (rs_max_rows(max_atoms, max_cells) + 2 * (size_t)nblk) * sizeof(double));
   L.total = o;
   return L;
 }
@@ -979,8 +1034,7 @@ int pme_real(const double* pos, const double* q, int N, const double box[9], dou
   a.list_lim = (float)(ru * ru + 4e-6 * eu * eu);
   a.slack = 0x1p-22 * eu;
   a.split = rs_split(N);
-  a.nblk = rs_nblk(N, a.nunit, a.split);
-  a.nrow = a.nunit * a.nblk;
+  a.nrow = rs_rows(N, a.nunit, a.split);
   a.N = N;
   a.n_count_blocks = (N + kRsCountThreads - 1) / kRsCountThreads;
   for (int d = 0; d < 3; ++d) {
@@ -1013,6 +1067,8 @@ int pme_real(const double* pos, const double* q, int N, const double box[9], dou
   a.rec = reinterpret_cast<double4*>(ws + W.rec);
   a.rec32 = reinterpret_cast<float4*>(ws + W.rec32);
   a.ridx = reinterpret_cast<int*>(ws + W.ridx);
+  a.groups = reinterpret_cast<int4*>(ws + W.groups);
+  a.ngroup = reinterpret_cast<int*>(ws + W.ngroup);
   a.rows = reinterpret_cast<double*>(ws + W.rows);
   hipStream_t s = static_cast<hipStream_t>(stream);
   const int nsub = a.ncell * kRsSlabs;
@@ -1034,13 +1090,15 @@ int pme_real(const double* pos, const double* q, int N, const double box[9], dou
       if (nsub > kRsTable)
         k_rs_fill<false><<<atoms, block, 0, s>>>(a);
       else
-        k_rs_fill<true><<<atoms, block, 0, s>>>(a);
+        k_rs_fill<true><<<dim3(a.n_count_blocks + 1), block, 0, s>>>(a);
     }
   }
-  if (a.ncheb == kRsChebShort)
-    launch_pairs<kRsChebShort>(a, s);
-  else
-    launch_pairs<kRsCheb>(a, s);
+  if (N > 0) {
+    if (a.ncheb == kRsChebShort)
+      launch_pairs<kRsChebShort>(a, s);
+    else
+      launch_pairs<kRsCheb>(a, s);
+  }
   k_rs_reduce<<<dim3(1), block, 0, s>>>(a);
   return hipGetLastError() == hipSuccess ? PME_OK : PME_EDEVICE;
 }
