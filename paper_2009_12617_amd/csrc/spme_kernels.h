@@ -816,6 +816,39 @@ __device__ __forceinline__ InflCol infl_col(const Args& a, int xp, const double*
   return c;
 }
 
+// One mode (xp, y, z) of an orthorhombic cell: returns G(m) F(m) and adds
+// the mode's energy/virial terms to acc.
+template <class G, typename T>
+__device__ __forceinline__ cplx<T> infl_ortho(const Args& a, const InflCol& c, int xp, int y,
+                                              int z, const double* bs, cplx<T> f, double* acc) {
+  constexpr int K1 = G::K1, K2 = G::K2, K3 = G::K3;
+  const int my = (2 * y <= K2) ? y : y - K2, mz = (2 * z <= K3) ? z : z - K3;
+  const double mvy = my * a.invL[1], mvz = mz * a.invL[2];
+  const double ny = (2 * y == K2) ? 0.0 : mvy, nz = (2 * z == K3) ? 0.0 : mvz;
+  // m = 0 carries no energy (G(0) = 0): its |m|^2 is replaced by 1 and its
+  // G by 0, without a branch
+  const bool m0 = (xp == 0) && (y == 0) && (z == 0);
+  const double msq = m0 ? 1.0 : fma(mvz, mvz, fma(mvy, mvy, c.mvx2));
+  // reciprocal by v_rcp_f64 and two Newton steps
+  double r = __builtin_amdgcn_rcp(msq);
+  r = fma(r, fma(-msq, r, 1.0), r);
+  r = fma(r, fma(-msq, r, 1.0), r);
+  const double gm = m0 ? 0.0 : c.A * bs[K1 + y] * bs[K1 + K2 + z] * r;  // G(m)
+  const double f2 = fma((double)f.x, (double)f.x, (double)f.y * (double)f.y);
+  const double e = c.wx * gm * f2;
+  const double eu = e * (r + c.fac);
+  const double eux = eu * c.mvx, euy = eu * mvy, eun = eu * c.nx;
+  acc[0] += e;
+  acc[1] = fma(eux, c.mvx, acc[1]);
+  acc[2] = fma(euy, mvy, acc[2]);
+  acc[3] = fma(eu * mvz, mvz, acc[3]);
+  acc[4] = fma(eun, ny, acc[4]);
+  acc[5] = fma(eun, nz, acc[5]);
+  acc[6] = fma(eu * ny, nz, acc[6]);
+  const T g = (T)gm;
+  return {f.x * g, f.y * g};
+}
+
 // The modes (xp, +-y, +-z) of an orthorhombic cell, 0 <= y <= K2/2 (YPAIR;
 // without it the modes (xp, y, +-z), any y) and 0 <= z <= K3/2: four modes of
 // one |m|^2 (two or one where an index is 0 or Nyquist).  The reciprocal,
@@ -935,7 +968,8 @@ __device__ __forceinline__ cplx<T> infl_general(const Args& a, const InflCol& c,
 }
 
 // The influence function on a whole column, element (y, z) at buf[z * PZ + y].
-// Orthorhombic: mirrored modes together (a 72 x 72 column 3.0 -> 1.4 us).
+// Orthorhombic: mirrored modes together (a 72 x 72 column 3.0 -> 1.4 us), but
+// on the smallest columns.
 // General cell: the exponential of each mode and sign is the cost; modes with
 // a Nyquist index, which need two to eight, come last and by themselves (dealt
 // in order they put one such mode into every wavefront), and in the columns
@@ -948,18 +982,21 @@ __device__ __forceinline__ void influence_column(const Args& a, cplx<typename P:
   constexpr int H2 = K2 / 2, H3 = K3 / 2;
   const InflCol c = infl_col<G>(a, xp, bs);
   auto at = [&](int y, int z) -> cplx<typename P::real>& { return buf[z * PZ + y]; };
+  if constexpr (K2 * K3 <= 256) {
+    // at most a wavefront per SIMD: nothing waits for its neighbours, and one
+    // mode per thread is the shorter chain (16^3 column, general cell: 6.4 us
+    // like this, 6.9 as below; orthorhombic: 5.6, 6.0)
+    for (int i = vt; i < K2 * K3; i += VT) {
+      const int y = i % K2, z = i / K2;
+      cplx<typename P::real>& f = at(y, z);
+      f = a.triclinic ? infl_general<G>(a, c, xp, y, z, bs, f, acc)
+                      : infl_ortho<G>(a, c, xp, y, z, bs, f, acc);
+    }
+    return;
+  }
   if (!a.triclinic) {
     for (int i = vt; i < (H2 + 1) * (H3 + 1); i += VT)
       infl_mirror<G, true>(a, c, xp, i % (H2 + 1), i / (H2 + 1), bs, at, acc);
-    return;
-  }
-  if constexpr (K2 * K3 <= 256) {
-    // at most a wavefront per SIMD: nothing waits for its neighbours (16^3
-    // column 6.4 us like this, 6.9 as below)
-    for (int i = vt; i < K2 * K3; i += VT) {
-      cplx<typename P::real>& f = at(i % K2, i / K2);
-      f = infl_general<G>(a, c, xp, i % K2, i / K2, bs, f, acc);
-    }
     return;
   }
   const bool self = xp == 0 || 2 * xp == K1;  // m and -m both in this column
