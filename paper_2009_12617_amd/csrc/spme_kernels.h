@@ -1067,13 +1067,18 @@ __device__ __forceinline__ void ev_row(const Args& a, double* acc, int r) {
 // workgroup (whatever its size): thread l adds rows l, l + 256, ..., then a
 // DPP sum over the lanes and the wavefronts' sums in order.  wred: 32 doubles
 // of LDS.  (By one wavefront the 2,080 rows of a split 128^3 column took 13 us.)
+// UNROLL rows of a thread are in flight at once: one in the interpolation,
+// whose few rows do not set its time and whose registers decide how many tiles
+// share a CU (four rows took a p = 4 tile from 64 to 72: three of them a CU for
+// four; batch of eight 64^3 systems, interpolation 18.8 -> 20.9 us).
 constexpr int kReduceThreads = 256;
+template <int UNROLL>
 static __device__ void reduce_ev(const Args& a, double* wred) {
   const int tid = threadIdx.x;
   const double* partial = reinterpret_cast<const double*>(a.ws + a.lay.partial);
   double v[7] = {0, 0, 0, 0, 0, 0, 0};
   if (tid < kReduceThreads) {
-#pragma unroll 4
+#pragma unroll UNROLL
     for (int r = tid; r < a.ev_rows; r += kReduceThreads) {
 #pragma unroll
       for (int c = 0; c < 7; ++c) v[c] += partial[r * 8 + c];
@@ -1289,7 +1294,7 @@ __global__ __launch_bounds__(kPassThreads) void k_conv_y(Args a_in, BatchArgs bt
   cplx<T>* tw = buf + CZ * PY;
   const int tid = threadIdx.x;
   if (DIR > 0 && blockIdx.x == (K1 / 2 + 1) * NZC) {
-    if (a.reduce_ev) reduce_ev(a, reinterpret_cast<double*>(smem));
+    if (a.reduce_ev) reduce_ev<4>(a, reinterpret_cast<double*>(smem));
     return;
   }
   const int xp = blockIdx.x / NZC, z0 = (blockIdx.x - xp * NZC) * CZ;
@@ -1711,7 +1716,7 @@ __global__ __launch_bounds__(kInterpThreads) void k_interp(Args a_in, BatchArgs 
   TRACE(3, 0);
   const int tid = threadIdx.x;
   if (blockIdx.x == K3 * NQ) {
-    if (a.reduce_ev) reduce_ev(a, reinterpret_cast<double*>(smem));
+    if (a.reduce_ev) reduce_ev<1>(a, reinterpret_cast<double*>(smem));
     return;
   }
   if (a.N == 0) return;
@@ -1817,7 +1822,10 @@ __global__ __launch_bounds__(kInterpThreads) void k_interp_phi(Args a_in, BatchA
   const int tid = threadIdx.x;
   if (blockIdx.x == K3 * NQ) {
     __shared__ double wred[32];
-    if (a.reduce_ev) reduce_ev(a, wred);
+    // (FP64, p = 6: with four rows in flight the compiler keeps the whole kernel
+    // to 128 registers, two tiles to a CU, with one it takes 132 to 134; a bound
+    // on the registers instead spills.  Eight 48^3 systems 77.2, 78.5 and 81.8 us)
+    if (a.reduce_ev) reduce_ev<(!P::fixed && ORDER == 6 ? 4 : 1)>(a, wred);
     return;
   }
   if (a.N == 0) return;

@@ -7,10 +7,10 @@
 
 namespace spme {
 
-// Sum of the energy/virial rows by one wavefront (pme_solve outside a step).
+// Sum of the energy/virial rows by one workgroup (pme_solve outside a step).
 __global__ __launch_bounds__(kReduceThreads) void k_reduce_ev(Args a) {
   __shared__ double wred[32];
-  reduce_ev(a, wred);
+  reduce_ev<4>(a, wred);
 }
 
 // Clears the bucket and overflow counts of a step whose binning ran without
