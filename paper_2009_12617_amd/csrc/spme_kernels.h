@@ -1067,11 +1067,16 @@ __device__ __forceinline__ void ev_row(const Args& a, double* acc, int r) {
 // workgroup (whatever its size): thread l adds rows l, l + 256, ..., then a
 // DPP sum over the lanes and the wavefronts' sums in order.  wred: 32 doubles
 // of LDS.  (By one wavefront the 2,080 rows of a split 128^3 column took 13 us.)
-// UNROLL rows of a thread are in flight at once: one in the interpolation,
-// whose few rows do not set its time and whose registers decide how many tiles
-// share a CU (four rows took a p = 4 tile from 64 to 72: three of them a CU for
-// four; batch of eight 64^3 systems, interpolation 18.8 -> 20.9 us).
+// UNROLL rows of a thread are in flight at once: interp_ev_rows in the
+// interpolation, else four.
 constexpr int kReduceThreads = 256;
+// Their registers are the interpolation tiles' too, and decide how many tiles
+// share a CU.  At p = 4 four rows take a tile from 64 to 72, three of them a CU
+// for four (batch of eight 64^3 systems, interpolation 18.8 -> 20.9 us); at
+// p = 6 the tile itself takes more, and FP64 after a split transform stays at
+// 128, two tiles a CU, only with four (one: 132 to 134, eight 48^3 systems 77.2
+// -> 78.5 us).
+__host__ __device__ constexpr int interp_ev_rows(int order) { return order == 6 ? 4 : 1; }
 template <int UNROLL>
 static __device__ void reduce_ev(const Args& a, double* wred) {
   const int tid = threadIdx.x;
@@ -1716,7 +1721,7 @@ __global__ __launch_bounds__(kInterpThreads) void k_interp(Args a_in, BatchArgs 
   TRACE(3, 0);
   const int tid = threadIdx.x;
   if (blockIdx.x == K3 * NQ) {
-    if (a.reduce_ev) reduce_ev<1>(a, reinterpret_cast<double*>(smem));
+    if (a.reduce_ev) reduce_ev<interp_ev_rows(ORDER)>(a, reinterpret_cast<double*>(smem));
     return;
   }
   if (a.N == 0) return;
@@ -1822,10 +1827,7 @@ __global__ __launch_bounds__(kInterpThreads) void k_interp_phi(Args a_in, BatchA
   const int tid = threadIdx.x;
   if (blockIdx.x == K3 * NQ) {
     __shared__ double wred[32];
-    // (FP64, p = 6: with four rows in flight the compiler keeps the whole kernel
-    // to 128 registers, two tiles to a CU, with one it takes 132 to 134; a bound
-    // on the registers instead spills.  Eight 48^3 systems 77.2, 78.5 and 81.8 us)
-    if (a.reduce_ev) reduce_ev<(!P::fixed && ORDER == 6 ? 4 : 1)>(a, wred);
+    if (a.reduce_ev) reduce_ev<interp_ev_rows(ORDER)>(a, wred);
     return;
   }
   if (a.N == 0) return;
