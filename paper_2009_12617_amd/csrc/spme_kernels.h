@@ -1141,7 +1141,7 @@ k_conv(Args a_in, BatchArgs bt) {
   // the first chunk's loads are issued before the tables are computed
   // (when they fit in a few registers)
   constexpr int EPT = (CZ * K2 + NT - 1) / NT;
-  constexpr bool PREFETCH = EPT * sizeof(cplx<T>) <= 80;
+  constexpr bool PREFETCH = NC == 1 && EPT * sizeof(cplx<T>) <= 80;
   cplx<T> first[PREFETCH ? EPT : 1];
   if constexpr (PREFETCH) {
 #pragma unroll
