@@ -547,8 +547,13 @@ __global__ __launch_bounds__(spread_threads<BATCH>()) void k_spread_x(Args a_in,
   // items: the records of the buckets one after another; kItems per thread
   // per pass so that their loads overlap.  (The bucket ends in scalar
   // registers: at p = 6 the kernel keeps to 64 vector registers, two
-  // workgroups to a CU; 128^3 p = 6 spreading 34.9 -> 30.6 us.)  At p = 4 a
-  // tile holds one to two records per thread, and two are enough.
+  // workgroups to a CU; 128^3 p = 6 spreading 34.9 -> 30.6 us.)  At p = 4 two
+  // in flight are enough: a liquid's tile holds one to two records per thread
+  // of a step on its own, about twice that batched.  Steps with two / four, us:
+  // 64^3 with 23,000 atoms 23.0 / 23.2, 130,000 34.8 / 35.3, 209,715 42.8 / 43.4;
+  // batched, 24 systems of 32x32x64 72.3 / 73.4, 64^3 134.6 / 136.4, 64x64x128
+  // 276.3 / 280.2 (two of them 55.7 / 55.2), 32 boxes of mixed size 145.8 /
+  // 149.3, three 46.9 / 45.8.
   constexpr int kItems = ORDER > 4 ? 4 : 2;
   int end[NBK];
 #pragma unroll
@@ -676,13 +681,17 @@ template <class P, class G>
 __host__ __device__ constexpr int conv_threads() {
   return (sizeof(typename P::real) == 8 && (G::K2 >= 72 || G::K3 >= 72)) ? 512 : 1024;
 }
-// Batched columns (FP32 precisions): 512 threads where that still covers
-// every FFT task of a pass (64-point pencils and shorter), so that two
-// columns share a CU.
+// Batched columns (FP32 precisions) up to 72 x 72: 512 threads, so that two or
+// more columns share a CU.  A phase of block_fft then takes two rounds (48 x 48:
+// 576 tasks, 72 x 72: 648), which is the better bargain once the chip is full.
+// Batched p = 4 steps at 512 / 1,024 threads, us: 24 systems of 24^3 36.0 / 39.8,
+// 36^3 59.6 / 64.0, 48^3 84.5 / 90.6, 72^3 170.8 / 176.1; eight of 48^3 44.9 /
+// 44.4, of 72^3 83.4 / 85.3; two of 48^3 30.4 / 29.9, of 72^3 46.6 / 42.6; 3 to 32
+// boxes of mixed size 46.9 / 49.0 and 145.8 / 150.7.  (Larger columns take the
+// split convolution.)
 template <class P, class G, bool BATCH>
 __host__ __device__ constexpr int conv_block() {
-  return (BATCH && P::fixed && conv_threads<P, G>() == 1024 && fft_lanes(G::K2) * G::K3 <= 512 &&
-          fft_lanes(G::K3) * G::K2 <= 512)
+  return (BATCH && P::fixed && G::K2 * G::K3 <= 72 * 72)
              ? 512
              : conv_threads<P, G>();
 }
