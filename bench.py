@@ -786,6 +786,8 @@ def main():
         ms_rs = start.elapsed_time(stop) / nrep
         nc = int(np.floor(fr.box[0, 0] / rcut))
         real = {"us_per_eval": ms_rs * 1e3, "rcut_A": rcut, "beta": w.beta, "cells": [nc] * 3,
+                # (clear, count, fill with the scan, pairs, energies: as many for any box
+                # of more than 8,192 atoms and up to 8,192 sub-cells, 8 to a cell)
                 "launches": 5, "what": "pme_real: FP64 erfc pair sum, self term, water exclusions"}
         last = (nrep - 1) % F
         atoms = np.random.default_rng(7).choice(N, size=64, replace=False)

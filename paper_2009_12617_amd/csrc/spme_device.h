@@ -96,6 +96,14 @@ __device__ __forceinline__ int scan32_add(int v) {
   return v;
 }
 
+// ... and over all 64 lanes.
+__device__ __forceinline__ int wave_scan_add(int v) {
+  v = scan32_add(v);  // (lanes 32 .. 63 likewise scan their two rows, the second still to come)
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0x8, 0xf, false);  // row_bcast 15 into row 3
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);  // row_bcast 31 into rows 2, 3
+  return v;
+}
+
 // wave_sums: an inclusive DPP scan of V doubles over the wavefront (rows,
 // then row_bcast 15 and 31); lane 63 ends with the wavefront's sums.
 // block_sums: sums over the block in a fixed order -- wave_sums, then the

@@ -165,17 +165,6 @@ hipError_t launch_conv(const Args& a, hipStream_t s, const Timing& t = Timing(),
 hipError_t launch_reduce_ev(const Args& a, hipStream_t s);
 hipError_t launch_inv_x(const Args& a, hipStream_t s, const Timing& t = Timing(),
                         const BatchArgs* bt = nullptr);
-// Whether one workgroup does the step of these inputs faster than the chain of
-// launches.  Measured at 16^3 (one launch / four, us): the grid and its
-// transforms cost the one workgroup 12 to 13 us (FP64 14, a general cell 4
-// more) and each of the N p^3 contributions its share of one CU's LDS atomics
-// --  p = 4: 64 atoms 12.8 / 17.8, 320 15.0 / 18.2, 576 17.4 / 18.7, 768
-//     18.5 / 18.9, 1024 20.3 / 19.2;  p = 6: 256 19.8 / 21.2, 320 22.0 / 21.6
-//     FP64: p = 4: 320 17.9 / 19.0, 448 19.3 / 19.3;  p = 6: 128 20.8 / 21.4,
-//     192 23.6 / 21.7
-//     general cell: p = 4: 320 19.4 / 19.5, 448 20.3 / 19.8; FP64 p = 4: 128
-//     19.3 / 19.6, 192 20.3 / 20.0
-// -- so the line is drawn on N p^2.  (24^3 lost at every size: 25 / 19.)
 // Atoms per binning workgroup of a step on its own, of the built-in choice.  Few
 // atoms: small workgroups spread over the CUs and start sooner.  Many: every
 // workgroup adds to most buckets' counters, so fewer of them.  Step at 256 /
@@ -188,6 +177,17 @@ hipError_t launch_inv_x(const Args& a, hipStream_t s, const Timing& t = Timing()
 constexpr int default_bin_chunk(int N) {
   return N <= 4608 ? 256 : N <= 28672 ? 512 : kBinThreads;
 }
+// Whether one workgroup does the step of these inputs faster than the chain of
+// launches.  Measured at 16^3 (one launch / four, us): the grid and its
+// transforms cost the one workgroup 12 to 13 us (FP64 14, a general cell 4
+// more) and each of the N p^3 contributions its share of one CU's LDS atomics
+// --  p = 4: 64 atoms 12.8 / 17.8, 320 15.0 / 18.2, 576 17.4 / 18.7, 768
+//     18.5 / 18.9, 1024 20.3 / 19.2;  p = 6: 256 19.8 / 21.2, 320 22.0 / 21.6
+//     FP64: p = 4: 320 17.9 / 19.0, 448 19.3 / 19.3;  p = 6: 128 20.8 / 21.4,
+//     192 23.6 / 21.7
+//     general cell: p = 4: 320 19.4 / 19.5, 448 20.3 / 19.8; FP64 p = 4: 128
+//     19.3 / 19.6, 192 20.3 / 20.0
+// -- so the line is drawn on N p^2.  (24^3 lost at every size: 25 / 19.)
 bool step_small_wins(const Args& a);
 hipError_t launch_step_small(const Args& a, hipStream_t s);
 hipError_t launch_interp(const Args& a, hipStream_t s, const Timing& t = Timing(),

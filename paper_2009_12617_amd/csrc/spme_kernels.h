@@ -363,7 +363,7 @@ __device__ __forceinline__ void rfft_inv(cplx<T>* v, int j, cplx<T>* scr, const 
 // the M-point complex transform of the packed sequence z_n = x_{2n} +
 // i x_{2n+1} runs in registers (rfft_fwd / rfft_inv, RX = M/8 lanes per row,
 // lane j holding points j + RX r), the packing identities of r2c_post and
-// c2r_pre go through the row in LDS.  The decomposition (radix 8, twiddles
+// c2r_mode go through the row in LDS.  The decomposition (radix 8, twiddles
 // W_M^(j s), radix RX) and the twiddle table entries are those of the
 // Stockham stages of fft_pencil for these lengths.
 template <int K1>
@@ -394,7 +394,7 @@ __device__ __forceinline__ void r2c_row_reg(cplx<T>* v, cplx<T>* row, int j, cpl
 
 // Inverse: the row (complex, in LDS) holds X_0 .. X_M of a real row; on
 // return it holds z_n = x_{2n} + i x_{2n+1}, n < M (unnormalised).  The
-// c2r_pre identity is formed per mode in registers (Im X_0, Im X_M dropped).
+// c2r_mode identity is formed per mode in registers (Im X_0, Im X_M dropped).
 template <typename T, int K1>
 __device__ __forceinline__ void c2r_row_reg(cplx<T>* row, int j, cplx<T>* scr, const cplx<T>* tw) {
   constexpr int M = K1 / 2, RX = M / 8, EX = 8 / RX;

@@ -264,25 +264,36 @@ __device__ __forceinline__ void list_groups(const RsArgs& a, Start&& start, unsi
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int most = kRsHome / a.split;
   auto groups_of = [&](int u) { return u < a.nunit ? ((int)(start(u + 1) - start(u)) + most - 1) / most : 0; };
+  auto put = [&](int i, int per, int4 g) { a.groups[i % per * kXcds + i / per] = g; };
+  // the n groups of unit u, from the i-th on
+  auto put_unit = [&](int u, int n, int i, int per) {
+    if (n == 0) return;
+    const int u0 = (int)start(u), u1 = (int)start(u + 1), gs = (u1 - u0 + n - 1) / n;
+    for (int k = 0; k < n; ++k) put(i + k, per, make_int4(u0 + k * gs, min(u0 + (k + 1) * gs, u1), u, 0));
+  };
+  auto put_rest = [&](int total, int per, int first, int step) {
+    for (int i = total + first; i < per * kXcds; i += step) put(i, per, make_int4(0, 0, 0, 0));
+    if (first == 0) *a.ngroup = per * kXcds;
+  };
+  if (a.nunit <= 64) {  // one wavefront, without a barrier (small systems: a microsecond of the sort)
+    if (wave != NT / 64 - 1) return;
+    const int n = groups_of(lane), inc = wave_scan_add(n);
+    const int total = __builtin_amdgcn_readlane(inc, 63), per = (total + kXcds - 1) / kXcds;
+    put_unit(lane, n, inc - n, per);
+    put_rest(total, per, lane, 64);
+    return;
+  }
   int mine = 0;
   for (int u = tid; u < a.nunit; u += NT) mine += groups_of(u);
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) mine += __shfl_xor(mine, d);
-  if (lane == 0) wsum[wave] = (unsigned)mine;
+  mine = wave_scan_add(mine);
+  if (lane == 63) wsum[wave] = (unsigned)mine;
   __syncthreads();
   int total = 0;
   for (int w = 0; w < NT / 64; ++w) total += (int)wsum[w];
   const int per = (total + kXcds - 1) / kXcds;
-  auto put = [&](int i, int4 g) { a.groups[i % per * kXcds + i / per] = g; };
   int carry = 0;
   for (int b = 0; b < a.nunit; b += NT) {
-    const int u = b + tid, n = groups_of(u);
-    int inc = n;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      const int o = __shfl_up(inc, d);
-      if (lane >= d) inc += o;
-    }
+    const int u = b + tid, n = groups_of(u), inc = wave_scan_add(n);
     __syncthreads();  // the previous sums are read
     if (lane == 63) wsum[wave] = (unsigned)inc;
     __syncthreads();
@@ -291,14 +302,9 @@ __device__ __forceinline__ void list_groups(const RsArgs& a, Start&& start, unsi
       if (w < wave) i += (int)wsum[w];
       carry += (int)wsum[w];
     }
-    if (n > 0) {
-      const int u0 = (int)start(u), u1 = (int)start(u + 1), gs = (u1 - u0 + n - 1) / n;
-      for (int k = 0; k < n; ++k)
-        put(i + k, make_int4(u0 + k * gs, min(u0 + (k + 1) * gs, u1), u, 0));
-    }
+    put_unit(u, n, i, per);
   }
-  for (int i = total + tid; i < per * kXcds; i += NT) put(i, make_int4(0, 0, 0, 0));
-  if (tid == 0) *a.ngroup = per * kXcds;
+  put_rest(total, per, tid, NT);
 }
 
 // Small systems (at most PER atoms per thread and kRsSortTable sub-cells): workgroup 0
@@ -530,7 +536,7 @@ __global__ __launch_bounds__(kRsThreads, S == 1 ? 3 : 2) void k_rs_pairs(RsArgs 
   // x, y, z (with the periodic shift), |position - centre|^2 and charge, in
   // arrays of their own: a record's 32 bytes would meet 8 bank groups, these
   // 8-byte reads meet 32 (43 conflict cycles a read against 3, by the counters)
-  constexpr int kPlane = (kStage + 16 * S + 31) / 32 * 32 + 16;  // (test: the planes' banks alternate)
+  constexpr int kPlane = (kStage + 16 * S + 31) / 32 * 32 + 16;  // (consecutive planes start half the banks apart)
   __shared__ double stage[5][kPlane];
   __shared__ unsigned list[kRsList];    // record | segment << kRsIdxBits
   __shared__ unsigned masks_all[kRsWaves][kWords + 2][64];  // two words of zeros at the end
@@ -841,7 +847,7 @@ __global__ __launch_bounds__(kRsThreads, S == 1 ? 3 : 2) void k_rs_pairs(RsArgs 
       }
     }
     if (g4 == 0 && col < nh && spl == 0) {
-      const bool add = a.accumulate || a.excl_off != nullptr;  // (k_rs_fill wrote the exclusions)
+      const bool add = a.accumulate || a.excl_off != nullptr;  // (k_rs_sort or k_rs_count wrote the exclusions)
       double* out = a.forces + 3 * (size_t)a.ridx[own];
 #pragma unroll
       for (int d = 0; d < 3; ++d) out[d] = add ? out[d] + f[d] : f[d];
@@ -916,8 +922,7 @@ RsLayout rs_layout(int max_atoms, int max_cells) {
   L.start = o;   o = align256(o + (nsub + 1) * sizeof(unsigned));
   L.rank = o;    o = align256(o + (size_t)max_atoms * sizeof(unsigned));
   L.rec = o;     o = align256(o + (size_t)max_atoms * sizeof(double4));
-  // (tiles of 16 read past the last record of a cell)
-  L.rec32 = o;   o = align256(o + ((size_t)max_atoms + kRsGroup) * sizeof(float4));
+  L.rec32 = o;   o = align256(o + (size_t)max_atoms * sizeof(float4));
   L.ridx = o;    o = align256(o + (size_t)max_atoms * sizeof(int));
   L.groups = o;  o = align256(o + rs_max_rows(max_atoms, max_cells) * sizeof(int4));
   L.ngroup = o;  o = align256(o + sizeof(int));
