@@ -257,8 +257,8 @@ constexpr int kXcds = 8;
 // chip as a uniform one does (a fixed number of workgroups per unit, from the
 // mean density, took the groups of dense units one after the other: 65,535
 // atoms in a slab across a tenth of its box 646 us, now 180; a uniform box 146,
-// now 143).  XCD x takes
-// a contiguous eighth of the groups.  start(u): first atom of unit u.
+// now 143).  XCD x takes a contiguous eighth of the groups.  start(u): first
+// atom of unit u.
 template <int NT, class Start>
 __device__ __forceinline__ void list_groups(const RsArgs& a, Start&& start, unsigned* wsum) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -516,9 +516,10 @@ using f32x4 = __attribute__((__vector_size__(4 * sizeof(float)))) float;
 // 84, and as much again to find each lane's share.)
 //
 // What bounds it: FP64 issue, about 65 of the 80 instructions of an evaluation;
-// 65,535 atoms at 9 A: 205 -> 134 us, of which the instructions take 75 at full
-// rate and the listing and staging of candidates most of the rest.  Measured
-// and not taken, us per evaluation of the whole term (149 now): records read
+// 65,535 atoms at 9 A: 223 -> 141 us by the profiler, of which the instructions
+// take 75 at full rate and the listing and staging of candidates most of the
+// rest.  Measured and not taken, us per evaluation of the whole term where this
+// form took 149 (143 now, with the groups listed from the counts): records read
 // from the vector cache, 165; one wavefront per workgroup and group, 208; each
 // pair once with the candidates' forces summed in LDS, 175 (64-bit LDS atomics,
 // and half-neighbourhoods differ too much between lanes).
@@ -892,10 +893,11 @@ void launch_pairs(const RsArgs& a, hipStream_t s) {
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 // Wavefronts sharing a group of 16 home atoms: enough workgroups to occupy the
-// chip, no more (each repeats the listing of candidates).  Measured at rcut 8
-// to 9 A, us per evaluation for 1 / 2 / 4: 52 / 41 / 35 at 2,100 atoms, 62 / 48
-// / 48 at 4,095, 61 / 57 / 61 at 11,100, 73 / 68 / 72 at 15,000, 69 / 73 / 89 at
-// 21,000, 153 / 188 / 239 at 65,535.
+// chip, no more (each repeats the listing of candidates).  Measured at rcut 9 A,
+// us per evaluation for 1 / 2 / 4: 50 / 40 / 35 at 2,100 atoms, 62 / 47 / 48 at
+// 4,095, 66 / 60 / 68 at 11,100, 68 / 62 / 81 at 15,000, 78 / 75 / 80 at 16,400,
+// 83 / 81 / 97 at 21,000, 81 / 90 / 104 at 26,000, 150 / 176 / 223 at 65,535
+// (between 16,000 and 21,000 one and two are within 4%).
 int rs_split(int N) { return N <= 5120 ? 4 : N <= 16384 ? 2 : 1; }
 
 // Pair workgroups launched: no fewer than the groups that list_groups makes of
