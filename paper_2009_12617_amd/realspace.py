@@ -28,6 +28,7 @@ class RealSpace:
         self._ws = raw[off:off + nbytes]
         self._nbytes = nbytes
         self._excl_ok = None  # exclusion tensors last checked
+        self._excl_kept = None
 
     def __call__(self, pos, q, box, beta, rcut, exclusions=None, coulomb=1.0, forces=None,
                  accumulate=False, stream=None):
@@ -56,13 +57,14 @@ class RealSpace:
                 raise ValueError("exclusion offsets must have length N+1")
             # the partner list must hold exactly the entries the offsets index
             # (the kernels read off[0..N]); checked with one host read per
-            # pair of tensors and contents, then remembered
+            # pair of tensors and contents, then remembered -- with the tensors,
+            # so that no others can take their addresses
             key = (off.data_ptr(), idx.data_ptr(), idx.numel(), off._version, idx._version)
             if key != self._excl_ok:
                 ends = off[[0, -1]].cpu()
                 if int(ends[0]) != 0 or int(ends[1]) != idx.numel():
                     raise ValueError("exclusion offsets must start at 0 and end at len(partners)")
-                self._excl_ok = key
+                self._excl_ok, self._excl_kept = key, (off, idx)
         s = stream if stream is not None else torch.cuda.current_stream(self.device)
         check(self._lib.pme_real(pos.data_ptr(), q.data_ptr(), n, bp, float(beta), float(rcut),
                                  float(coulomb), off.data_ptr() if off is not None else None,
