@@ -106,9 +106,13 @@ unsigned variants_for(int K1, int K2, int K3, int order, int precision) {
 // Built-in choices (measured on MI355X): one workgroup per column wherever a
 // column has fewer than 8192 points (each extra launch costs more than the
 // LDS work it spreads out) -- the register-resident transforms where the
-// pencils allow them (FP32, 32 or 64 points), else the LDS-resident ones --
-// and the fused interpolation except for p >= 6 on grids with K2 K3 >= 16384
-// (where redoing the inverse x transform per bin costs 6.8x the grid).
+// pencils allow them (32 or 64 points), else the LDS-resident ones -- and the
+// fused interpolation except for p >= 6 on grids with K2 K3 >= 16384 (where
+// redoing the inverse x transform per bin costs 6.8x the grid).  Split / fused
+// columns above the line, us per p = 4 step: 64x64x128 37.5 / 39.5 (general cell
+// 43.6 / 47.9, FP64 50.6 / 52.0), 128^3 72.6 / 70.2 (general cell 85 / 96, FP64
+// 126 / 136); 96^3 lies above it too, 56.2 / 49.0 (general cell 64.9 / 58.8, FP64
+// 80.4 / 77.7): there an autotuned plan takes the fused column.
 void default_variants(int K1, int K2, int K3, int order, int precision, int* conv_mode,
                       int* interp_mode) {
   const unsigned v = variants_for(K1, K2, K3, order, precision);
